@@ -13,14 +13,24 @@
 //            flushed from the recent ring are copied from it instead.
 //            Values (new or ring) -> LDS.
 //   phase B  two lanes per (token, K|V) group, half the channels each:
-//            exact top-k of |x| with a median-of-three insertion network
-//            (each lane over its half, then its partner's list merged in),
-//            the type-7 quantile, fp16 scale/zero and the codes.  Key codes
-//            go straight to their words; value codes go to LDS.
+//            exact top-k of |x| by packed 16-bit sorting and merging networks
+//            (select.h), the type-7 quantile, fp16 scale/zero and the codes.
+//            Key codes go straight to their words; value codes go to LDS.
 //   phase C  value-code words (each spans 8 tokens) are assembled from LDS;
 //            words only partly covered by this call are merged with what the
 //            page already holds.
 //   phase D  bf16 window writes (sink and ring) and the optional k~ output.
+//
+// Bound by the vector units (78% busy at 4 x 16384 tokens with the fused
+// normalisation: about 1370 vector instructions a wave, 300 of them the
+// normalisation and rotation, 350-460 the selection, 400 the codes), not by
+// its bytes.  That prefill takes 118 us a call where 148 us went before the
+// selection ran on packed networks (1770 instructions), the value words were
+// assembled from 4-byte reads and byte permutes, T_K was requested with the
+// keys instead of after their normalisation, the gain came through LDS, rows
+// that are not new were no longer branched around, and the flush and counter
+// launches were folded into one (below); a 5 x 5000-token 4-bit one 38 us
+// instead of 43.
 #include "common.h"
 #include "merge.h"
 #include "quantise.h"
@@ -36,24 +46,38 @@ __global__ void __launch_bounds__(256, 4) append_kernel(AppendArgs a)
     constexpr int kPitch = D + 8;  // bf16 elements per LDS row (16 B pad)
     __shared__ __attribute__((aligned(16))) uint16_t kt[kPage * kPitch];
     __shared__ __attribute__((aligned(16))) uint16_t vt[kPage * kPitch];
-    __shared__ int32_t sh_page[1];  // page index
     __shared__ int32_t sh_cnt[3];   // the sequence's counters (read_counters)
+    __shared__ __attribute__((aligned(16))) float sh_gain[ROPE ? 4 * D : 4];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
-    // XCD-aware order.  The device hands consecutive workgroups to its 8
-    // XCDs in turn (workgroup L runs on XCD L % 8), so the 8 workgroups of a
-    // turn take 8 consecutive tiles of one (head, sequence), and the next
-    // turns take the same 8 tiles for the other heads and sequences: the
-    // rotary-table rows of a tile's positions are read into one XCD's L2 and
-    // reused there by every head and sequence.  gridDim.x is a multiple of 8.
-    const uint32_t wg = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-    const uint32_t hbs = gridDim.y * gridDim.z, turn = wg / 8;
-    const int tile = (int)(8 * (turn / hbs) + wg % 8);
-    const int h = (int)((turn % hbs) % gridDim.y), b = (int)((turn % hbs) / gridDim.y);
+    const bool windows_only = a.mode == kModeWindow;
+    int tile, h, b;
+    if (windows_only) {
+        tile = blockIdx.x;
+        h = blockIdx.y;
+        b = blockIdx.z;
+    } else {
+        // XCD-aware order.  The device hands consecutive workgroups to its 8
+        // XCDs in turn (workgroup L runs on XCD L % 8), so the 8 workgroups of
+        // a turn take 8 consecutive tiles of one (head, sequence), and the next
+        // turns take the same 8 tiles for the other heads and sequences: the
+        // rotary-table rows of a tile's positions are read into one XCD's L2
+        // and reused there by every head and sequence.  gridDim.x is a multiple
+        // of 8.
+        const uint32_t wg = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+        const uint32_t hbs = gridDim.y * gridDim.z, turn = wg / 8;
+        tile = (int)(8 * (turn / hbs) + wg % 8);
+        h = (int)((turn % hbs) % gridDim.y);
+        b = (int)((turn % hbs) / gridDim.y);
+    }
+    // the gain, requested before anything that waits for the counters
+    f32x4 gain4 = {0.f, 0.f, 0.f, 0.f};
+    if (ROPE && a.gain != nullptr && lane < D / 4) gain4 = reinterpret_cast<const f32x4 *>(a.gain)[lane];
 
     // ---- per-sequence bookkeeping (identical in every workgroup)
-    const SeqCounters cnt = read_counters(a, b, a.max_new, sh_cnt, tid);
+    const SeqCounters cnt = a.arrivals > 0 ? read_counters(a, b, a.max_new, sh_cnt, tid)
+                                           : plain_counters(a, b, a.max_new);
     const int32_t s_old = cnt.s_old, q_old = cnt.q_old, nn = cnt.nn;
     const int32_t s_new = s_old + nn;
     const int32_t q_new = next_quant_end(s_new, q_old, a.s_sink, a.s_keep, a.s_flush);
@@ -61,9 +85,14 @@ __global__ void __launch_bounds__(256, 4) append_kernel(AppendArgs a)
     const int32_t first = s_old < start_old ? s_old : start_old;
     const int32_t ring = a.win_slots - a.s_sink;
 
-    // ---- which tile
-    int k0 = first < a.s_sink ? (first / kPage) - a.sink_tiles : (first - a.s_sink) / kPage;
-    const int k = k0 + tile;
+    // ---- which tile: of the positions from the first one that is new or due
+    // or, to write the windows, the sink and the positions after q_new
+    int k;
+    if (windows_only)
+        k = tile < a.sink_tiles ? tile - a.sink_tiles
+                                : (max(q_new, a.s_sink) - a.s_sink) / kPage + tile - a.sink_tiles;
+    else
+        k = (first < a.s_sink ? (first / kPage) - a.sink_tiles : (first - a.s_sink) / kPage) + tile;
     int32_t blk_lo, blk_hi;
     if (k < 0) {
         blk_lo = (k + a.sink_tiles) * kPage;
@@ -72,13 +101,25 @@ __global__ void __launch_bounds__(256, 4) append_kernel(AppendArgs a)
         blk_lo = a.s_sink + k * kPage;
         blk_hi = blk_lo + kPage;
     }
-    const bool do_new = (a.mode & kModeNew) != 0, do_flush = (a.mode & kModeFlush) != 0;
+    // A sequence with nothing in its ring (an empty one above all) has no
+    // position whose slot a new one could take before it is flushed: the
+    // quantising launch then writes its windows as well, and the window
+    // launch only its counters.
+    const bool ring_empty = start_old >= s_old;
+    const bool do_windows = (a.mode & kModeNew) != 0 || (windows_only ? !ring_empty : a.mode == kModeQuant && ring_empty);
+    const bool do_new = (a.mode & (kModeNew | kModeQuant)) != 0 || do_windows;
+    const bool do_flush = (a.mode & (kModeFlush | kModeQuant)) != 0;
     int32_t lo = max(blk_lo, first), hi = min(blk_hi, s_new);
-    if (!do_new) {
+    if (windows_only) {
+        lo = do_windows ? max(lo, k < 0 ? s_old : max(s_old, q_new)) : hi;
+    } else if (!do_new) {
         // a flush-only launch touches nothing but the ring positions that
         // are due: [start_old, q_new) below s_old (an empty cache has none)
         lo = max(lo, start_old);
         hi = min(hi, min(s_old, q_new));
+    } else if (!do_windows && a.k_tilde_out == nullptr) {
+        lo = max(lo, start_old);
+        hi = min(hi, q_new);
     }
     if (lo >= hi) {
         commit_finish(a, b, commit_arrive(a, b, s_old, q_old, nn, tid), s_new, q_new, tid);
@@ -89,19 +130,16 @@ __global__ void __launch_bounds__(256, 4) append_kernel(AppendArgs a)
     // start_old <= p < q_new; otherwise a window entry (sink, or ring if new).
     auto is_new = [&](int32_t p) { return p >= s_old; };
     auto quant_now = [&](int32_t p) {
-        return p >= start_old && p < q_new && (is_new(p) ? do_new : do_flush);
+        return !windows_only && p >= start_old && p < q_new && (is_new(p) ? do_new : do_flush);
     };
     auto window_write = [&](int32_t p) {
-        return do_new && is_new(p) && (p < a.s_sink || p >= q_new);
+        return do_windows && is_new(p) && (p < a.s_sink || p >= q_new);
     };
 
-    if (tid == 0) {
-        int32_t phys = -1;
-        if (k >= 0 && k < a.max_pages) {
-            phys = a.page_table[(int64_t)b * a.max_pages + k];
-            if (phys < 0 || phys >= a.n_pages) phys = -1;
-        }
-        sh_page[0] = phys;
+    int32_t page = -1;  // the tile's physical page
+    if (k >= 0 && k < a.max_pages) {
+        page = a.page_table[(int64_t)b * a.max_pages + k];
+        if (page < 0 || page >= a.n_pages) page = -1;
     }
 
     const int64_t head_win = ((int64_t)b * a.n_kv + h) * a.win_slots;  // win_k row base (slots)
@@ -116,82 +154,84 @@ __global__ void __launch_bounds__(256, 4) append_kernel(AppendArgs a)
     uint4 vpre[kVPer];
     auto load_values = [&]() {
         // the thread's chunks lie kVRows token rows apart in v_new: one
-        // element offset, then a constant step (negative for rows before
-        // the new ones, which are not loaded)
+        // element offset, then a constant step (a row that is not new loads
+        // the first row instead, which is in bounds and not used)
         const int r0v = tid / kVec, cv = tid % kVec;
         const int64_t step = (int64_t)kVRows * a.n_kv * D;
         const int64_t off0 = (((int64_t)b * a.max_new + (blk_lo + r0v - s_old)) * a.n_kv + h) * D + 8 * cv;
 #pragma unroll
         for (int q = 0; q < kVPer; ++q) {
             const int32_t p = blk_lo + r0v + kVRows * q;
-            if (p >= lo && p < hi && do_new && is_new(p))
-                vpre[q] = *reinterpret_cast<const uint4 *>(a.v_new + (off0 + q * step));
+            const bool ld = p >= lo && p < hi && is_new(p);
+            vpre[q] = *reinterpret_cast<const uint4 *>(a.v_new + (ld ? off0 + q * step : (int64_t)0));
         }
     };
-    if constexpr (!ROPE) load_values();
-
-    // ---- phase A: transformed keys -> kt, values -> vt
     // the tile's new positions are [new_lo, hi); window writes go to those
     // below s_sink or at or above q_new
     const int32_t new_lo = max(lo, s_old);
     const bool any_new = do_new && new_lo < hi;
-    const bool any_window = any_new && (new_lo < a.s_sink || hi > q_new);
+    const bool any_window = do_windows && any_new && (new_lo < a.s_sink || hi > q_new);
+    if (!ROPE && any_new) load_values();
+
+    // ---- phase A: transformed keys -> kt, values -> vt
     if (any_new) {
         // Wave w produces output channels [w D/4, (w+1) D/4) for all 64 rows.
         constexpr int kNtW = D / 64;  // N-tiles per wave
         const int j = lane >> 4, n = lane & 15;
         constexpr bool fused = ROPE;
-        // this wave's rows of T_K, in flight while the keys are staged (the
-        // fused variant loads them after the normalisation: its registers
-        // are full until then)
         KeyTile<D, kNtW> xf;
-        if constexpr (!fused) xf.load(a.tk, h, wave * kNtW, lane);
         // phase A0: each new row once (wave w rows 16 w .. 16 w + 15, one
         // load per lane and chunk for the whole tile) into the value rows,
         // which serve as the key operand's staging until the values arrive:
         // RoPE(Norm(k)) rounded to bf16 when fused, else k as it came
-        // A row that is not new loads the first row of k_new (in bounds;
-        // it is replaced by zeros), so that every load of the tile is
-        // issued at once, with no branch between them.
+        // A row that is not new loads the first row of k_new (in bounds), so
+        // that every load of the tile is issued at once, with no branch
+        // between them; what it leads to is not used (the rows of a product
+        // do not mix).
         const int r0 = 16 * wave + n;
         const int32_t p0 = blk_lo + r0;
-        const bool ld0 = (p0 >= lo && p0 < hi && is_new(p0) && do_new);
+        const bool ld0 = p0 >= lo && p0 < hi && is_new(p0);
         const uint16_t *krow0 =
             a.k_new + (ld0 ? (((int64_t)b * a.max_new + (p0 - s_old)) * a.n_kv + h) * D : (int64_t)0);
         u32x4 kin[L::kChunks];
 #pragma unroll
         for (int c = 0; c < L::kChunks; ++c) kin[c] = *reinterpret_cast<const u32x4 *>(krow0 + 32 * c + 8 * j);
+        float rt[D / 64][16];
+        if constexpr (fused) load_rope<D>(a, j, ld0 ? p0 : 0, rt);
+        // this wave's rows of T_K, in flight while the keys are normalised
+        // and staged
+        xf.load(a.tk, h, wave * kNtW, lane);
         if constexpr (!fused) {
 #pragma unroll
-            for (int c = 0; c < L::kChunks; ++c) {
-                const u32x4 zero = {0u, 0u, 0u, 0u};
-                *reinterpret_cast<u32x4 *>(vt + r0 * kPitch + 32 * c + 8 * j) = ld0 ? kin[c] : zero;
-            }
+            for (int c = 0; c < L::kChunks; ++c)
+                *reinterpret_cast<u32x4 *>(vt + r0 * kPitch + 32 * c + 8 * j) = kin[c];
         } else {
-            const int r = r0;
-            const bool ld = ld0;
-            float rt[D / 64][16];
-            load_rope<D>(a, j, ld ? p0 : 0, rt);
-            // (a row that is not new holds the first row of k_new here: its
-            // result is replaced by zeros below)
+            // the gain through LDS, a copy for each wave: no barrier stands
+            // between this and its use
+            const float *gain = nullptr;
+            if (a.gain != nullptr) {
+                float *mine = sh_gain + D * wave;
+                if (lane < D / 4) reinterpret_cast<f32x4 *>(mine)[lane] = gain4;
+                __builtin_amdgcn_wave_barrier();
+                gain = mine;
+            }
             float x[L::kChunks][8];
 #pragma unroll
             for (int c = 0; c < L::kChunks; ++c) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) x[c][e] = bf16_bits_to_f32((kin[c][e >> 1] >> (16 * (e & 1))) & 0xFFFFu);
             }
-            norm_rope_row<D>(x, j, rt, a);
+            norm_rope_row<D>(x, j, rt, gain, a.eps);
             load_values();
 #pragma unroll
             for (int c = 0; c < L::kChunks; ++c) {
                 u32x4 pk;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) pk[q] = ld ? pack_bf16_rne(x[c][2 * q], x[c][2 * q + 1]) : 0u;
-                *reinterpret_cast<u32x4 *>(vt + r * kPitch + 32 * c + 8 * j) = pk;
+                for (int q = 0; q < 4; ++q) pk[q] = pack_bf16_rne(x[c][2 * q], x[c][2 * q + 1]);
+                *reinterpret_cast<u32x4 *>(vt + r0 * kPitch + 32 * c + 8 * j) = pk;
             }
         }
         __syncthreads();
-        if constexpr (fused) xf.load(a.tk, h, wave * kNtW, lane);
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) {
             const int r = 16 * mt + n;  // A row handled by this lane
@@ -200,18 +240,12 @@ __global__ void __launch_bounds__(256, 4) append_kernel(AppendArgs a)
             for (int c = 0; c < L::kChunks; ++c)
                 aop[c] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(vt + r * kPitch + 32 * c + 8 * j));
             f32x4 acc[kNtW];
-            xf.apply(aop, acc);
+            xf.apply_rows(aop, acc);
+            // four consecutive channels of row r: one 8-byte write
 #pragma unroll
-            for (int nt = 0; nt < kNtW; ++nt) {
-                const int ch = (wave * kNtW + nt) * 16 + n;
-#pragma unroll
-                for (int rr = 0; rr < 4; rr += 2) {
-                    uint32_t pr = pack_bf16_rne(acc[nt][rr], acc[nt][rr + 1]);
-                    const int row = 16 * mt + 4 * j + rr;
-                    kt[row * kPitch + ch] = (uint16_t)(pr & 0xFFFFu);
-                    kt[(row + 1) * kPitch + ch] = (uint16_t)(pr >> 16);
-                }
-            }
+            for (int nt = 0; nt < kNtW; ++nt)
+                *reinterpret_cast<uint2 *>(kt + r * kPitch + (wave * kNtW + nt) * 16 + 4 * j) =
+                    make_uint2(pack_bf16_rne(acc[nt][0], acc[nt][1]), pack_bf16_rne(acc[nt][2], acc[nt][3]));
         }
         // the value rows are about to be overwritten: every wave must have
         // read its key operands from them
@@ -252,7 +286,6 @@ __global__ void __launch_bounds__(256, 4) append_kernel(AppendArgs a)
         }
     }
     __syncthreads();
-    const int32_t page = sh_page[0];
     uint8_t *pg = page >= 0 ? a.pages + ((int64_t)page * a.n_kv + h) * L::kPageBytes : nullptr;
 
     // ---- phases B and C
@@ -262,19 +295,21 @@ __global__ void __launch_bounds__(256, 4) append_kernel(AppendArgs a)
     const int32_t blk_end = blk_lo + kPage;
     const bool all_quant = lo <= blk_lo && blk_end <= hi && start_old <= blk_lo && blk_end <= q_new &&
                            (blk_end <= s_old || do_new) && (blk_lo >= s_old || do_flush);
-    quantise_tile<D, BITS>(a, kt, vt, blk_lo, [&](int32_t p) { return p >= lo && p < hi && quant_now(p); },
-                           all_quant, pg, tid);
+    if (!windows_only)
+        quantise_tile<D, BITS>(a, kt, vt, blk_lo, [&](int32_t p) { return p >= lo && p < hi && quant_now(p); },
+                               all_quant, pg, tid);
 
     // ---- phase D: bf16 windows and the optional k~ output (a tile of
     // the quantised region of a prefill has neither)
-    if (any_window || (any_new && a.k_tilde_out != nullptr)) {
+    const bool k_out = a.k_tilde_out != nullptr && !windows_only;
+    if (any_window || (any_new && k_out)) {
         constexpr int kVec = D / 8;
         for (int idx = tid; idx < kPage * kVec; idx += 256) {
             const int r = idx / kVec, cv = idx % kVec;
             const int32_t p = blk_lo + r;
             if (p < lo || p >= hi || !(do_new && is_new(p))) continue;
             const uint4 kv = *reinterpret_cast<const uint4 *>(kt + r * kPitch + 8 * cv);
-            if (a.k_tilde_out != nullptr)
+            if (k_out)
                 *reinterpret_cast<uint4 *>(
                     a.k_tilde_out + (((int64_t)b * a.max_new + (p - s_old)) * a.n_kv + h) * D + 8 * cv) = kv;
             if (window_write(p)) {
@@ -282,13 +317,15 @@ __global__ void __launch_bounds__(256, 4) append_kernel(AppendArgs a)
                 *reinterpret_cast<uint4 *>(a.win_k + (head_win + slot) * D + 8 * cv) = kv;
             }
         }
-        // values, channel-major: consecutive threads write consecutive slots
-        for (int idx = tid; any_window && idx < kPage * D; idx += 256) {
-            const int ch = idx / kPage, r = idx % kPage;
-            const int32_t p = blk_lo + r;
-            if (p < lo || p >= hi || !window_write(p)) continue;
+        // values, channel-major: consecutive threads write consecutive slots,
+        // each thread one position's
+        const int r = tid % kPage;
+        const int32_t p = blk_lo + r;
+        if (any_window && p >= lo && p < hi && window_write(p)) {
             const int32_t slot = p < a.s_sink ? p : ring_slot(p, a.s_sink, ring);
-            a.win_v[(head_win * D) + (int64_t)ch * a.win_slots + slot] = vt[r * kPitch + ch];
+            uint16_t *dst = a.win_v + head_win * D + slot;
+#pragma unroll 8
+            for (int ch = tid / kPage; ch < D; ch += 256 / kPage) dst[(int64_t)ch * a.win_slots] = vt[r * kPitch + ch];
         }
     }
     commit_finish(a, b, arrived, s_new, q_new, tid);
@@ -403,24 +440,6 @@ static hipError_t launch_append(const char *name, const AppendArgs &a, dim3 grid
     if (a.rope != nullptr) launch(name, append_kernel<D, BITS, true>, grid, dim3(256), s, a);
     else launch(name, append_kernel<D, BITS, false>, grid, dim3(256), s, a);
     return hipGetLastError();
-}
-
-// S and S_quant of every sequence advanced after an append launch of many
-// tiles, which then counts no arrivals (thousands of workgroups of one
-// sequence would queue their device-scope atomics at one address, and each
-// holds its slot until its own returns).  Launched after it on the stream,
-// so that every tile has read the old values.  One thread per sequence; the
-// new-token count is clamped as read_counters clamps it.
-__global__ void __launch_bounds__(256) append_commit_kernel(AppendArgs a, int32_t batch)
-{
-    const int b = (int)(blockIdx.x * 256 + threadIdx.x);
-    if (b >= batch) return;
-    const int32_t s_old = a.seq_len[b], q_old = a.quant_end[b];
-    int32_t nn = a.n_new[b];
-    nn = nn < 0 ? 0 : (nn > a.max_new ? a.max_new : nn);
-    const int32_t s_new = s_old + nn;
-    a.seq_len[b] = s_new;
-    a.quant_end[b] = next_quant_end(s_new, q_old, a.s_sink, a.s_keep, a.s_flush);
 }
 
 template <int D, int BITS>
@@ -558,39 +577,40 @@ static int append_impl(const wushkv_cache *c, const uint16_t *k_new, const uint1
     dim3 grid((unsigned)tiles, (unsigned)c->n_kv_heads, (unsigned)c->batch);
 
     // Flushed ring slots may be reused by new tokens of the same call only if
-    // the ring is shorter than the span; then flush first, in its own launch.
-    // That launch only touches positions already in the ring, which span at
-    // most the ring's length from the first unflushed one.
+    // the ring is shorter than the span.  One launch does it all where it is
+    // not; otherwise either the flush goes first, in its own launch (it only
+    // touches positions already in the ring, which span at most the ring's
+    // length from the first unflushed one), or the window writes last.
     const int64_t ring = (int64_t)c->win_slots - c->s_sink;
     const bool fused = ring >= span;
     const dim3 flush_grid((unsigned)std::min<int64_t>(tiles, (a.sink_tiles + (ring + kPage - 1) / kPage + 1 + 7) / 8 * 8),
                           grid.y, grid.z);
 
-    // The launch that appends the new tokens advances the counters (its
-    // workgroups are the last to read them): its last arriving workgroup
-    // does, or, beyond kArrivalsMax workgroups per sequence, a launch of its
-    // own right after it.
+    // The launch that writes the new window entries advances the counters
+    // (its workgroups are the last to read them): its last arriving workgroup
+    // does.  Beyond kArrivalsMax workgroups per sequence the arrivals would
+    // queue (thousands of device-scope atomics at one address, each holding
+    // its workgroup's slot until its own returns: 8 us of a 4 x 16384-token
+    // prefill), so there the first launch quantises (kModeQuant, which needs
+    // no arrivals and no flush before it) and a small one writes the windows'
+    // at most s_keep + s_flush - 1 positions (and the sink), where the first
+    // could not, and the counters.  Two launches instead of flush, append and
+    // a launch for the counters.
     constexpr int64_t kArrivalsMax = 64;
-    auto go = [&](int mode) -> hipError_t {
+    const bool by_halves = tiles * c->n_kv_heads > kArrivalsMax;
+    const int64_t wtiles = a.sink_tiles + ((int64_t)c->s_keep + c->s_flush - 1 + kPage - 1) / kPage + 1;
+    if (wtiles * c->n_kv_heads > 0x7FFFFFFF) return WUSHKV_EINVAL;
+    auto go = [&](int mode, const char *name, dim3 g) -> hipError_t {
         a.mode = mode;
-        const char *name = mode == kModeFlush ? "append_flush" : "append_kernel";
-        const dim3 g = mode == kModeFlush ? flush_grid : grid;
-        const bool commit_launch = (mode & kModeNew) && (int64_t)g.x * g.y > kArrivalsMax;
-        a.arrivals = (mode & kModeNew) && !commit_launch ? (int32_t)(g.x * g.y) : 0;
+        a.arrivals = (mode & (kModeNew | kModeWindow)) ? (int32_t)(g.x * g.y) : 0;
         const int key = c->head_dim * 10 + storage_bits(c->bits);
-        hipError_t e = hipErrorInvalidValue;
         switch (key) {
-            case 1282: e = launch_append<128, 2>(name, a, g, s); break;
-            case 1284: e = launch_append<128, 4>(name, a, g, s); break;
-            case 642: e = launch_append<64, 2>(name, a, g, s); break;
-            case 644: e = launch_append<64, 4>(name, a, g, s); break;
+            case 1282: return launch_append<128, 2>(name, a, g, s);
+            case 1284: return launch_append<128, 4>(name, a, g, s);
+            case 642: return launch_append<64, 2>(name, a, g, s);
+            case 644: return launch_append<64, 4>(name, a, g, s);
         }
-        if (e == hipSuccess && commit_launch) {
-            launch("append_commit", append_commit_kernel, dim3((unsigned)((c->batch + 255) / 256)), dim3(256), s, a,
-                   (int32_t)c->batch);
-            e = hipGetLastError();
-        }
-        return e;
+        return hipErrorInvalidValue;
     };
     hipError_t e;
     if (max_new <= kStepMax) {
@@ -603,11 +623,14 @@ static int append_impl(const wushkv_cache *c, const uint16_t *k_new, const uint1
             case 642: e = launch_append_step<64, 2>(a, sgrid, s); break;
             default: e = launch_append_step<64, 4>(a, sgrid, s); break;
         }
+    } else if (by_halves) {
+        e = go(kModeQuant, "append_kernel", grid);
+        if (e == hipSuccess) e = go(kModeWindow, "append_commit", dim3((unsigned)wtiles, grid.y, grid.z));
     } else if (fused) {
-        e = go(kModeFlush | kModeNew);
+        e = go(kModeFlush | kModeNew, "append_kernel", grid);
     } else {
-        e = go(kModeFlush);
-        if (e == hipSuccess) e = go(kModeNew);
+        e = go(kModeFlush, "append_flush", flush_grid);
+        if (e == hipSuccess) e = go(kModeNew, "append_kernel", grid);
     }
     if (e != hipSuccess) return WUSHKV_ELAUNCH;
     return WUSHKV_OK;

@@ -203,6 +203,19 @@ struct KeyTile {
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) acc[nt] = mfma16(aop[c], bop[nt][c], acc[nt]);
     }
+    // The same products with the operands exchanged, so that a lane ends
+    // with consecutive channels of one row: row n, output channel
+    // 16 (nt0 + nt) + 4 j + r in acc[nt][r].  Every element is the same sum
+    // of the same products in the same order, bit for bit.
+    __device__ __forceinline__ void apply_rows(const bf16x8 (&aop)[kC], f32x4 (&acc)[NT]) const
+    {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < kC; ++c)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) acc[nt] = mfma16(bop[nt][c], aop[c], acc[nt]);
+    }
 };
 
 // floor(a / b) for b > 0.

@@ -7,10 +7,16 @@
 #include <type_traits>
 
 #include "common.h"
+#include "select.h"
 
 namespace wushkv {
 
-enum { kModeFlush = 1, kModeNew = 2 };
+// What an append launch does: quantise the ring positions that are due
+// (kModeFlush), append the new tokens (kModeNew: quantise those that are due,
+// write the others to the windows), or, for a large append, one half each of
+// both: kModeQuant quantises every due position, from the ring or new, and
+// kModeWindow then writes the windows.
+enum { kModeFlush = 1, kModeNew = 2, kModeQuant = 4, kModeWindow = 8 };
 
 struct AppendArgs {
     uint8_t *pages;
@@ -70,7 +76,7 @@ __device__ __forceinline__ void load_rope(const AppendArgs &a, int j, int32_t po
 
 template <int D>
 __device__ __forceinline__ void norm_rope_row(float (&x)[D / 32][8], int j, const float (&rt)[D / 64][16],
-                                              const AppendArgs &a)
+                                              const float *gain, float eps)
 {
     constexpr int kC = D / 32;
     float ss = 0.0f;
@@ -80,17 +86,17 @@ __device__ __forceinline__ void norm_rope_row(float (&x)[D / 32][8], int j, cons
         for (int e = 0; e < 8; ++e) ss = fmaf(x[c][e], x[c][e], ss);
     ss += __shfl_xor(ss, 16);
     ss += __shfl_xor(ss, 32);
-    const float r = 1.0f / sqrtf(ss / (float)D + a.eps);
+    const float r = 1.0f / sqrtf(ss / (float)D + eps);
     // (x r) g, or x r with no gain (a product by 1 is exact)
 #pragma unroll
     for (int c = 0; c < kC; ++c)
 #pragma unroll
         for (int e = 0; e < 8; ++e) x[c][e] = x[c][e] * r;
-    if (a.gain != nullptr) {
+    if (gain != nullptr) {
 #pragma unroll
         for (int c = 0; c < kC; ++c) {
-            const float4 g0 = *reinterpret_cast<const float4 *>(a.gain + 32 * c + 8 * j);
-            const float4 g1 = *reinterpret_cast<const float4 *>(a.gain + 32 * c + 8 * j + 4);
+            const float4 g0 = *reinterpret_cast<const float4 *>(gain + 32 * c + 8 * j);
+            const float4 g1 = *reinterpret_cast<const float4 *>(gain + 32 * c + 8 * j + 4);
             const float g[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
 #pragma unroll
             for (int e = 0; e < 8; ++e) x[c][e] = x[c][e] * g[e];
@@ -112,7 +118,7 @@ __device__ __forceinline__ void norm_rope_row(float (&x)[D / 32][8], int j, int3
 {
     float rt[D / 64][16];
     load_rope<D>(a, j, pos, rt);
-    norm_rope_row<D>(x, j, rt, a);
+    norm_rope_row<D>(x, j, rt, a.gain, a.eps);
 }
 
 // Sequence b's counters as they stand before this launch: thread 0 reads
@@ -138,6 +144,14 @@ __device__ __forceinline__ SeqCounters read_counters(const AppendArgs &a, int b,
     return c;
 }
 
+// The same in a launch that reports no arrivals: every wave reads them.
+__device__ __forceinline__ SeqCounters plain_counters(const AppendArgs &a, int b, int32_t max_nn)
+{
+    SeqCounters c{a.seq_len[b], a.quant_end[b], a.n_new[b]};
+    c.nn = c.nn < 0 ? 0 : (c.nn > max_nn ? max_nn : c.nn);
+    return c;
+}
+
 // Sequence b's counters advance from inside the launch that last reads
 // them.  Each workgroup reports once, after its reads of seq_len and
 // quant_end have returned (the values are tied to the report's operand), to
@@ -148,8 +162,8 @@ __device__ __forceinline__ SeqCounters read_counters(const AppendArgs &a, int b,
 // of the sequence has read the old values before the last one arrives, so
 // none can see the new ones: the other waves of a workgroup use thread 0's
 // reads (read_counters).  Thread 0 only; a launch with a.arrivals = 0 leaves
-// the counters alone (a launch of many workgroups per sequence does, and
-// append_commit_kernel advances them after it).
+// the counters alone (the quantising launch of a large append does, and the
+// window launch after it advances them).
 __device__ __forceinline__ int32_t commit_arrive(const AppendArgs &a, int b, int32_t s_old, int32_t q_old,
                                                  int32_t nn, int tid)
 {
@@ -168,55 +182,6 @@ __device__ __forceinline__ void commit_finish(const AppendArgs &a, int b, int32_
     __hip_atomic_store(a.commit + b, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// max and min of two values as medians of three against an infinity held in
-// a register (inf: +inf for the max, -inf for the min): one instruction
-// each, where fmaxf / fminf first quiet an operand that might be a
-// signalling NaN, a second instruction per call.  Equal to fmaxf / fminf for
-// every non-NaN operand.  The infinity comes from opaque_inf: a literal one
-// would be folded back into fmaxf / fminf.
-__device__ __forceinline__ float opaque_inf(bool negative)
-{
-    float v = negative ? -INFINITY : INFINITY;
-    asm volatile("" : "+v"(v));
-    return v;
-}
-__device__ __forceinline__ float max_m3(float x, float y, float pinf) { return __builtin_amdgcn_fmed3f(x, y, pinf); }
-__device__ __forceinline__ float min_m3(float x, float y, float ninf) { return __builtin_amdgcn_fmed3f(x, y, ninf); }
-
-// Descending top-KMAX of the values pushed so far; t[0] is the largest.
-// Inserting a into a sorted list is one median-of-three per slot:
-// new t[i] = med3(t[i-1], t[i], a), and new t[0] = max(t[0], a).
-template <int KMAX>
-struct TopK {
-    float t[KMAX];
-    float pinf;
-    __device__ __forceinline__ void init()
-    {
-#pragma unroll
-        for (int i = 0; i < KMAX; ++i) t[i] = -1.0f;
-        pinf = opaque_inf(false);
-    }
-    __device__ __forceinline__ void push(float a)
-    {
-#pragma unroll
-        for (int i = KMAX - 1; i >= 1; --i) t[i] = __builtin_amdgcn_fmed3f(t[i - 1], t[i], a);
-        t[0] = max_m3(t[0], a, pinf);
-    }
-    // t[k] for a runtime k, as a chain of selects.  The empty assembly step
-    // keeps the chain in registers: without it the compiler turns the chain
-    // into an indexed load from a private (scratch) copy of the list.
-    __device__ __forceinline__ float get(int k) const
-    {
-        float r = t[0];
-#pragma unroll
-        for (int i = 1; i < KMAX; ++i) {
-            r = (k == i) ? t[i] : r;
-            asm volatile("" : "+v"(r));
-        }
-        return r;
-    }
-};
-
 // The value of the partner lane (lane ^ 1): the two lanes of a pair share
 // one quantisation group, half of its elements each.
 __device__ __forceinline__ float pair_swap(float x)
@@ -225,56 +190,88 @@ __device__ __forceinline__ float pair_swap(float x)
                                                               0xF, false));
 }
 
+// |x| of a bf16 magnitude's pattern; -1 for the place of a NaN.
+__device__ __forceinline__ float magnitude(int16_t bits)
+{
+    return bits < 0 ? -1.0f : bf16_bits_to_f32((uint32_t)bits);
+}
+
 // a_lo and a_{lo+1} of the ascending sort of |x| over a bf16 row in LDS,
 // for lo = D - K (a_lo is the K-th largest), with the row's min and max.
-// The lane pair (2 r, 2 r + 1) shares row r: each lane keeps the sorted top
-// K of |x| over its half of the row.  The top K of the whole row are then
-// max(t[i], t'[K-1-i]), i < K, with t' the partner's list (a descending list
-// against an ascending one: each pair's larger value is in the top K of the
-// union, and each smaller one is not); a_lo and a_{lo+1} are the smallest and
-// the second smallest of these.  Both lanes form the same multiset.
+// The lane pair (2 r, 2 r + 1) shares row r, half of it each; both lanes end
+// with the same values.
+//
+// The vector units bound the append, so the row stays in its 16-bit form:
+// each register's half words (even and odd channels) are two lists selected
+// side by side by packed networks (select.h), whose top-K lists are merged
+// across the lane pair and then across the halves, the last step only as far
+// as the two smallest of the top K.  Per element that is 4.3 instructions
+// at K = 7 and 6 at K = 12 (one v_med3 per list slot and element before: 9
+// and 14).
+//
+// Extremes: bf16 patterns sort like the fp16 numbers with the same bits, so
+// the packed fp16 maximum3 / minimum3 fold two registers per instruction.
+// Patterns that are fp16 NaNs (|x| above 2^121, infinities, NaNs) come out as
+// one: their rows take a slower path on the floats themselves, where a NaN
+// counts for nothing (its magnitude sorts below every other, as -1).
 template <int D, int K>
 __device__ __forceinline__ void order_stats_topk(const uint16_t *row, int hf, float &a_lo, float &a_hi,
                                                  float &mn, float &mx)
 {
-    TopK<K> tk;
-    tk.init();
-    mn = INFINITY;
-    mx = -INFINITY;
+    constexpr int kRegs = D / 4;  // registers of half a row, two elements each
     const uint16_t *half = row + hf * (D / 2);
-#pragma unroll 4
-    for (int c8 = 0; c8 < D / 16; ++c8) {
-        uint4 v = *reinterpret_cast<const uint4 *>(half + 8 * c8);
-        uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    uint32_t w[kRegs];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
+    for (int c8 = 0; c8 < kRegs / 4; ++c8) {
+        const u32x4 v = *reinterpret_cast<const u32x4 *>(half + 8 * c8);
 #pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
-                float x = bf16_bits_to_f32(hh ? (w[q] >> 16) : (w[q] & 0xFFFFu));
-                mn = fminf(mn, x);
-                mx = fmaxf(mx, x);
-                tk.push(fabsf(x));
-            }
-        }
+        for (int q = 0; q < 4; ++q) w[4 * c8 + q] = v[q];
     }
-    const float ninf = opaque_inf(true);
-    float c[K];
+    auto swap32 = [](auto x) {
+        return __builtin_bit_cast(decltype(x), pair_swap(__builtin_bit_cast(float, x)));
+    };
+    f16x2 top = __builtin_bit_cast(f16x2, w[0]), bot = top;
 #pragma unroll
-    for (int i = 0; i < K; ++i) c[i] = max_m3(tk.t[i], pair_swap(tk.t[K - 1 - i]), tk.pinf);
-    if constexpr (K == 1) {
-        a_lo = a_hi = c[0];
-    } else {
-        float m1 = min_m3(c[0], c[1], ninf), m2 = max_m3(c[0], c[1], tk.pinf);
-#pragma unroll
-        for (int i = 2; i < K; ++i) {
-            m2 = __builtin_amdgcn_fmed3f(m1, m2, c[i]);  // m1 <= m2: the new second smallest
-            m1 = min_m3(m1, c[i], ninf);
-        }
-        a_lo = m1;
-        a_hi = m2;
+    for (int i = 1; i < kRegs; ++i) {
+        top = __builtin_elementwise_maximum(top, __builtin_bit_cast(f16x2, w[i]));
+        bot = __builtin_elementwise_minimum(bot, __builtin_bit_cast(f16x2, w[i]));
     }
-    mn = fminf(mn, pair_swap(mn));
-    mx = fmaxf(mx, pair_swap(mx));
+    top = __builtin_elementwise_maximum(top, swap32(top));
+    bot = __builtin_elementwise_minimum(bot, swap32(bot));
+    const uint32_t hi = __builtin_bit_cast(uint16_t, __builtin_elementwise_maximum(top[0], top[1]));
+    const uint32_t lo = __builtin_bit_cast(uint16_t, __builtin_elementwise_minimum(bot[0], bot[1]));
+    mx = bf16_bits_to_f32(hi);
+    mn = bf16_bits_to_f32(lo);
+    i16x2 x[kRegs];
+#pragma unroll
+    for (int i = 0; i < kRegs; ++i) x[i] = __builtin_bit_cast(i16x2, w[i] & 0x7FFF7FFFu);
+    if (__any((hi & 0x7FFFu) > 0x7C00u)) {
+        asm volatile("");  // a branch: this is not to be run and selected from
+        mn = INFINITY;
+        mx = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < kRegs; ++i) {
+            const float f0 = bf16_bits_to_f32(w[i] & 0xFFFFu), f1 = bf16_bits_to_f32(w[i] >> 16);
+            mn = fminf(fminf(mn, f0), f1);
+            mx = fmaxf(fmaxf(mx, f0), f1);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) x[i][e] = x[i][e] > 0x7F80 ? (int16_t)-1 : x[i][e];
+        }
+        mn = fminf(mn, pair_swap(mn));
+        mx = fmaxf(mx, pair_swap(mx));
+    }
+    i16x2 t[K], c[K], o[K];
+    top_k<K>(x, t);
+#pragma unroll
+    for (int i = 0; i < K; ++i) o[i] = swap32(t[i]);
+    top_of_two(t, o, c);
+    bitonic_sort(c);
+#pragma unroll
+    for (int i = 0; i < K; ++i) o[i] = i16x2{c[i][1], c[i][0]};
+    top_of_two(c, o, t);
+    bitonic_sort(t);
+    a_lo = magnitude(t[K - 1][0]);
+    a_hi = K > 1 ? magnitude(t[K > 1 ? K - 2 : 0][0]) : a_lo;
 }
 
 // Same order statistics by counting ranks: any lo, O(D^2) work.  Used when
@@ -334,15 +331,25 @@ __device__ __forceinline__ void quant_params(float a_lo, float a_hi, float t, bo
     inv = (s > 0.0f) ? 1.0f / s : 0.0f;
 }
 
-// clamp(rne((x - z) inv), 0, levels).  Clamping to [0, levels] before the
-// rounding gives the same integer (levels is an integer), and adding 2^23 to
-// a value in [0, 2^23) rounds it to an integer in the default
-// nearest-even mode, leaving that integer in the low bits of the sum.
-__device__ __forceinline__ uint32_t code_of(float x, float z, float inv, float levels)
+// clamp(rne((x - z) inv), 0, levels) + kCodeBias.  Clamping to [0, levels]
+// before the rounding gives the same integer (levels is an integer), and
+// adding 2^23 to a value in [0, 2^23) rounds it to an integer in the default
+// nearest-even mode, leaving that integer in the low bits of the sum, over
+// the bits of 2^23.  The bias stays: words add up biased codes shifted to
+// their places (one v_lshl_add_u32 each) and start from minus the sum of the
+// shifted biases (code_word_start), modulo 2^32.
+constexpr uint32_t kCodeBias = 0x4B000000u;
+// word + (code << bit) for a constant bit, in one instruction (left to
+// itself the compiler shifts, then adds in threes).
+__device__ __forceinline__ void add_code(uint32_t &word, uint32_t code, int bit)
+{
+    asm("v_lshl_add_u32 %0, %1, %2, %0" : "+v"(word) : "v"(code), "i"(bit));
+}
+__device__ __forceinline__ uint32_t biased_code_of(float x, float z, float inv, float levels)
 {
     const float y = (x - z) * inv;
     const float c = __builtin_amdgcn_fmed3f(y, 0.0f, levels);
-    return __float_as_uint(c + 8388608.0f) - 0x4B000000u;
+    return __float_as_uint(c + 8388608.0f);
 }
 
 // Eq. (5) (QuEST) parameters of a group held by a lane pair (this lane's
@@ -391,11 +398,16 @@ __device__ __forceinline__ void quest_params(const uint16_t *row, int hf, double
     quest_finish<D>(ss, coef, h_levels, s16, z16, z, inv);
 }
 
-// clamp(floor(x inv) + 2^(bits-1), 0, levels) of Eq. (5), as code_of.
-__device__ __forceinline__ uint32_t quest_code_of(float x, float inv, float h, float levels)
+// clamp(floor(x inv) + h, 0, levels) - h of Eq. (5), h = 2^(bits-1): the
+// clamp to [-h, levels - h + 1/2] first, then the floor with the conversion
+// to an integer in one instruction.  (A NaN clamps to the lower end, code 0.)
+// Words start from h at every code's place, as with kCodeBias.
+__device__ __forceinline__ uint32_t biased_quest_code_of(float x, float inv, float h, float levels)
 {
-    const float c = __builtin_amdgcn_fmed3f(floorf(x * inv) + h, 0.0f, levels);
-    return __float_as_uint(c + 8388608.0f) - 0x4B000000u;
+    const float y = __builtin_amdgcn_fmed3f(x * inv, -h, levels - h + 0.5f);
+    uint32_t c;
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(c) : "v"(y));
+    return c;
 }
 
 // The selection for K = D - lo: the top-K lists for K = KC .. 16 (each its
@@ -429,22 +441,39 @@ __device__ void value_words(uint16_t *vt, int32_t blk_lo, Pred quant, bool full,
     using L = Layout<D, BITS>;
     constexpr int kPitch = D + 8;
     if (full) {
+        // Four channels a thread: it reads their code bytes of a token as
+        // one word, gathers the tokens whose codes share byte k of the
+        // output words into word k (the codes leave the upper bits of their
+        // bytes free, and no field of a word crosses a byte), and transposes
+        // the four words' bytes: 16 reads and 20 vector instructions for
+        // four 2-bit words, where a byte read and a shift-or per code took 64.
         uint32_t *vreg = reinterpret_cast<uint32_t *>(pg + L::kRegionBytes);
-        constexpr int kWords = 64 * L::kWordsPerLane;
+        constexpr int kU = 2 * L::kNw;       // words of a lane and 32-token slice
+        constexpr int kItems = 2 * kU * 16;  // (32-token slice, j, four channels, u)
         constexpr int kRowBytes = 2 * kPitch;
-        for (int idx = tid; idx < kWords; idx += 256) {
-            const int Ln = idx / L::kWordsPerLane, rem = idx % L::kWordsPerLane;
-            const int kc = rem / (2 * L::kNw), u = rem % (2 * L::kNw);
-            const int j = Ln >> 4, m = Ln & 15;
+        for (int idx = tid; idx < kItems; idx += 256) {
+            const int u = idx % kU, m0 = 4 * ((idx / kU) & 3), j = (idx / (4 * kU)) & 3, kc = idx / (16 * kU);
             const uint8_t *base = vcode_row<D>(vt, 32 * kc + 8 * j);  // token i at + i kRowBytes
-            uint32_t bits = 0;
+            uint32_t g[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
             for (int e = 0; e < L::kCodesPerWord; ++e) {
                 const int o = e >> 3, i = e & 7;
-                const int ch = 16 * (u * L::kOpsPerWord + o) + m;
-                bits |= (uint32_t)base[i * kRowBytes + ch + (ch >= D / 2 ? D / 2 : 0)] << L::v_bit(o, i);
+                const int ch = 16 * (u * L::kOpsPerWord + o) + m0;
+                const uint32_t codes =
+                    *reinterpret_cast<const uint32_t *>(base + i * kRowBytes + ch + (ch >= D / 2 ? D / 2 : 0));
+                g[L::v_bit(o, i) / 8] |= codes << (L::v_bit(o, i) % 8);
             }
-            vreg[L::v_word(Ln, rem)] = bits;
+            // bytes (0, 1) and (2, 3) of each pair of words interleaved, then
+            // the halves joined: word c is byte c of g[0 .. 3]
+            const uint32_t a0 = __builtin_amdgcn_perm(g[1], g[0], 0x05010400u);
+            const uint32_t a1 = __builtin_amdgcn_perm(g[1], g[0], 0x07030602u);
+            const uint32_t b0 = __builtin_amdgcn_perm(g[3], g[2], 0x05010400u);
+            const uint32_t b1 = __builtin_amdgcn_perm(g[3], g[2], 0x07030602u);
+            const uint32_t word[4] = {
+                __builtin_amdgcn_perm(b0, a0, 0x05040100u), __builtin_amdgcn_perm(b0, a0, 0x07060302u),
+                __builtin_amdgcn_perm(b1, a1, 0x05040100u), __builtin_amdgcn_perm(b1, a1, 0x07060302u)};
+#pragma unroll
+            for (int c = 0; c < 4; ++c) vreg[L::v_word(16 * j + m0 + c, kc * kU + u)] = word[c];
         }
     } else if (pg != nullptr) {
         uint32_t *vreg = reinterpret_cast<uint32_t *>(pg + L::kRegionBytes);
@@ -520,7 +549,7 @@ __device__ void quantise_tile(const AppendArgs &a, const uint16_t *kt, uint16_t 
             constexpr int kHalf = D / 2;
             const int c0 = hf * kHalf;  // first channel of this lane's half
             // the code loops, instantiated once per codec's code formula
-            auto write_codes = [&](auto code_fn) {
+            auto write_codes = [&](uint32_t code_bias, auto code_fn) {
                 if (!is_v) {
                     // key words of this token: lane group jj = ch / 32 holds
                     // BITS words per token (see Layout::k_pos); this half covers
@@ -529,7 +558,16 @@ __device__ void quantise_tile(const AppendArgs &a, const uint16_t *kt, uint16_t 
 #pragma unroll
                     for (int jl = 0; jl < D / 64; ++jl)
 #pragma unroll
-                        for (int w = 0; w < BITS; ++w) kw[jl][w] = 0u;
+                        for (int w = 0; w < BITS; ++w) {
+                            uint32_t ones = 0u;  // a one at each code's place
+#pragma unroll
+                            for (int e = 0; e < 32 / BITS; ++e) {
+                                int word, bit;
+                                L::k_pos(0, e, word, bit);
+                                ones += 1u << bit;
+                            }
+                            kw[jl][w] = 0u - code_bias * ones;
+                        }
 #pragma unroll
                     for (int c8 = 0; c8 < kHalf / 8; ++c8) {
                         uint4 v = *reinterpret_cast<const uint4 *>(row + c0 + 8 * c8);
@@ -541,7 +579,7 @@ __device__ void quantise_tile(const AppendArgs &a, const uint16_t *kt, uint16_t 
                             const int cl = 8 * c8 + i;  // channel c0 + cl
                             int word, bit;
                             L::k_pos(r, c0 + cl, word, bit);
-                            kw[cl >> 5][(cl & 31) / (32 / BITS)] |= code << bit;
+                            add_code(kw[cl >> 5][(cl & 31) / (32 / BITS)], code, bit);
                         }
                     }
                     uint32_t *kreg = reinterpret_cast<uint32_t *>(pg);
@@ -555,13 +593,12 @@ __device__ void quantise_tile(const AppendArgs &a, const uint16_t *kt, uint16_t 
                     for (int c8 = 0; c8 < kHalf / 8; ++c8) {
                         uint4 v = *reinterpret_cast<const uint4 *>(row + c0 + 8 * c8);
                         uint32_t wv[4] = {v.x, v.y, v.z, v.w};
-                        uint32_t lo4 = 0, hi4 = 0;
+                        uint32_t lo4 = 0u - code_bias * 0x01010101u, hi4 = lo4;
 #pragma unroll
                         for (int i = 0; i < 8; ++i) {
                             uint32_t hb = (i & 1) ? (wv[i >> 1] >> 16) : (wv[i >> 1] & 0xFFFFu);
                             uint32_t code = code_fn(bf16_bits_to_f32(hb));
-                            if (i < 4) lo4 |= code << (8 * i);
-                            else hi4 |= code << (8 * (i - 4));
+                            add_code(i < 4 ? lo4 : hi4, code, 8 * (i & 3));
                         }
                         // over bytes of this lane's half of the row that it has read
                         *reinterpret_cast<uint2 *>(vcode_row<D>(vt, r) + hf * D + 8 * c8) = make_uint2(lo4, hi4);
@@ -571,10 +608,10 @@ __device__ void quantise_tile(const AppendArgs &a, const uint16_t *kt, uint16_t 
             const float kLv = (float)kLevels;
             if (quest) {
                 // Eq. (5): clamp(floor(x inv) + 2^(bits-1))
-                write_codes([&](float x) { return quest_code_of(x, inv, kMid, kLv); });
+                write_codes(0u - (uint32_t)((kLevels + 1) / 2), [&](float x) { return biased_quest_code_of(x, inv, kMid, kLv); });
             } else {
                 // Eq. (7): clamp(rne((x - z) inv))
-                write_codes([&](float x) { return code_of(x, z, inv, kLv); });
+                write_codes(kCodeBias, [&](float x) { return biased_code_of(x, z, inv, kLv); });
             }
         }
     }
@@ -606,41 +643,89 @@ __device__ __forceinline__ float row16_swap(float x)
     return __builtin_bit_cast(float, row16_swap<kStep>(__builtin_bit_cast(uint32_t, x)));
 }
 
-// The exact top-KMAX of |x|, min and max over a group held by 16 lanes,
-// kPer elements each: every lane keeps the top KMAX of its elements, then
-// inserts its partner's list at each of the four exchange steps, so that
-// every lane ends with the top KMAX of the whole group (the same multiset as
-// the lane-pair selection finds, hence the same order statistics).
-template <int KMAX, int kPer>
-__device__ __forceinline__ void few_order_stats(const float (&x)[kPer], int K, float &a_lo, float &a_hi,
+// The descending top min(K, 2 N) of a lane's list t[0 .. N - 1] and its
+// partner's at exchange step kStep.
+template <int kStep, int K, int N>
+__device__ __forceinline__ void merge_lanes(const i16x2 (&t)[N], i16x2 (&c)[K < 2 * N ? K : 2 * N])
+{
+    i16x2 o[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        o[i] = __builtin_bit_cast(i16x2, row16_swap<kStep>(__builtin_bit_cast(uint32_t, t[i])));
+    if constexpr (K <= N) {
+        static_assert(K == N, "lists hold at most K");
+        top_of_two(t, o, c);
+        bitonic_sort(c);
+    } else {
+        // all of both lists: a descending one, then an ascending one
+        i16x2 all[2 * N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            all[i] = t[i];
+            all[N + i] = o[N - 1 - i];
+        }
+        bitonic_sort(all);
+#pragma unroll
+        for (int i = 0; i < (K < 2 * N ? K : 2 * N); ++i) c[i] = all[i];
+    }
+}
+
+// The order statistics of order_stats_topk over a group held by 16 lanes,
+// two elements to each of a lane's kRegs registers: the half words' lists are
+// sorted in the lane, merged over the four exchange steps (every lane ends
+// with the top K of its half words' lists), then across the halves.  (As
+// median insertions of the partner's list at each step: 730 dependent
+// instructions at K = 12, 8 channels a lane; these networks: 260.)
+template <int K, int kRegs>
+__device__ __forceinline__ void few_order_stats(const uint32_t (&w)[kRegs], float &a_lo, float &a_hi,
                                                 float &mn, float &mx)
 {
-    TopK<KMAX> tk;
-    tk.init();
     mn = INFINITY;
     mx = -INFINITY;
+    i16x2 x[kRegs];
 #pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-        mn = fminf(mn, x[e]);
-        mx = fmaxf(mx, x[e]);
-        tk.push(fabsf(x[e]));
+    for (int i = 0; i < kRegs; ++i) {
+        const float f0 = bf16_bits_to_f32(w[i] & 0xFFFFu), f1 = bf16_bits_to_f32(w[i] >> 16);
+        mn = fminf(fminf(mn, f0), f1);
+        mx = fmaxf(fmaxf(mx, f0), f1);
+        x[i] = __builtin_bit_cast(i16x2, w[i] & 0x7FFF7FFFu);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) x[i][e] = x[i][e] > 0x7F80 ? (int16_t)-1 : x[i][e];  // (a NaN)
     }
-    auto step = [&](auto st) {
+    auto extremes = [&](auto st) {
         constexpr int kStep = decltype(st)::value;
-        float other[KMAX];
-#pragma unroll
-        for (int i = 0; i < KMAX; ++i) other[i] = row16_swap<kStep>(tk.t[i]);
-#pragma unroll
-        for (int i = 0; i < KMAX; ++i) tk.push(other[i]);
         mn = fminf(mn, row16_swap<kStep>(mn));
         mx = fmaxf(mx, row16_swap<kStep>(mx));
     };
-    step(std::integral_constant<int, 0>{});
-    step(std::integral_constant<int, 1>{});
-    step(std::integral_constant<int, 2>{});
-    step(std::integral_constant<int, 3>{});
-    a_lo = tk.get(K - 1);
-    a_hi = (K >= 2) ? tk.get(K - 2) : a_lo;
+    extremes(std::integral_constant<int, 0>{});
+    extremes(std::integral_constant<int, 1>{});
+    extremes(std::integral_constant<int, 2>{});
+    extremes(std::integral_constant<int, 3>{});
+    constexpr int k0 = K < kRegs ? K : kRegs, k1 = K < 2 * k0 ? K : 2 * k0, k2 = K < 2 * k1 ? K : 2 * k1,
+                  k3 = K < 2 * k2 ? K : 2 * k2, k4 = K < 2 * k3 ? K : 2 * k3;
+    static_assert(k4 == K, "16 lanes hold at least K of each half");
+    sort_blocks<0, kRegs>(x);
+    i16x2 t0[k0], t1[k1], t2[k2], t3[k3], t[K], o[K], c[K];
+#pragma unroll
+    for (int i = 0; i < k0; ++i) t0[i] = x[i];
+    merge_lanes<0, K>(t0, t1);
+    merge_lanes<1, K>(t1, t2);
+    merge_lanes<2, K>(t2, t3);
+    merge_lanes<3, K>(t3, t);
+#pragma unroll
+    for (int i = 0; i < K; ++i) o[i] = i16x2{t[i][1], t[i][0]};
+    top_of_two(t, o, c);
+    bitonic_sort(c);
+    a_lo = magnitude(c[K - 1][0]);
+    a_hi = K > 1 ? magnitude(c[K > 1 ? K - 2 : 0][0]) : a_lo;
+}
+
+template <int kRegs, int KC = 1>
+__device__ __forceinline__ void few_order_stats_of(int K, const uint32_t (&w)[kRegs], float &a_lo, float &a_hi,
+                                                   float &mn, float &mx)
+{
+    if (K == KC) few_order_stats<KC>(w, a_lo, a_hi, mn, mx);
+    else if constexpr (KC < 16) few_order_stats_of<kRegs, KC + 1>(K, w, a_lo, a_hi, mn, mx);
 }
 
 // Phases B and C for at most 8 positions [lo, hi) of the tile at blk_lo (one
@@ -669,18 +754,17 @@ __device__ void quantise_few(const AppendArgs &a, uint16_t *kt, uint16_t *vt, in
     if ((g & 7) < hi - lo && pg != nullptr) {  // uniform over the group's 16 lanes
         uint16_t *row = (is_v ? vt : kt) + r * kPitch;
         const int ch0 = kPer * sl;
-        float x[kPer];
+        uint32_t w[kPer / 2];
         if constexpr (kPer == 8) {
             const uint4 v = *reinterpret_cast<const uint4 *>(row + ch0);
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] = bf16_bits_to_f32((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xFFFFu));
+            w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
         } else {
             const uint2 v = *reinterpret_cast<const uint2 *>(row + ch0);
-            const uint32_t w[2] = {v.x, v.y};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) x[e] = bf16_bits_to_f32((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xFFFFu));
+            w[0] = v.x; w[1] = v.y;
         }
+        float x[kPer];
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) x[e] = bf16_bits_to_f32((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xFFFFu));
         uint32_t s16, z16;
         float z, inv;
         const bool quest = a.codec == WUSHKV_CODEC_QUEST;
@@ -703,12 +787,8 @@ __device__ void quantise_few(const AppendArgs &a, uint16_t *kt, uint16_t *vt, in
         } else {
             const int qlo = is_v ? a.lo_v : a.lo_k;
             const float qt = is_v ? a.t_v : a.t_k;
-            const int K = D - qlo;
             float a_lo, a_hi, mn, mx;
-            if (K <= 4) few_order_stats<4, kPer>(x, K, a_lo, a_hi, mn, mx);
-            else if (K <= 8) few_order_stats<8, kPer>(x, K, a_lo, a_hi, mn, mx);
-            else if (K <= 12) few_order_stats<12, kPer>(x, K, a_lo, a_hi, mn, mx);
-            else few_order_stats<16, kPer>(x, K, a_lo, a_hi, mn, mx);
+            few_order_stats_of(D - qlo, w, a_lo, a_hi, mn, mx);
             quant_params(a_lo, a_hi, qt, qlo + 1 < D, mn, mx, kLevels, s16, z16, z, inv);
         }
         if (sl == 0)
@@ -718,7 +798,8 @@ __device__ void quantise_few(const AppendArgs &a, uint16_t *kt, uint16_t *vt, in
         const float kLv = (float)kLevels;
 #pragma unroll
         for (int e = 0; e < kPer; ++e)
-            code[e] = quest ? quest_code_of(x[e], inv, kHalf, kLv) : code_of(x[e], z, inv, kLv);
+            code[e] = quest ? biased_quest_code_of(x[e], inv, kHalf, kLv) + (uint32_t)((kLevels + 1) / 2)
+                            : biased_code_of(x[e], z, inv, kLv) - kCodeBias;
         if (!is_v) {
             // this lane's channels lie in one key word: word w of 32-channel
             // chunk jc; the lanes sharing the word OR their bits together
