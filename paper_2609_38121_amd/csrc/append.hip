@@ -350,6 +350,7 @@ __global__ void __launch_bounds__(256) append_step_kernel(AppendArgs a)
     constexpr int kPitch = D + 8;
     constexpr int kNtW = D / 64;  // 16-channel output tiles per wave
     __shared__ __attribute__((aligned(16))) uint16_t kn[kStepMax * kPitch];
+    __shared__ __attribute__((aligned(16))) uint16_t vn[kStepMax * kPitch];  // the new values
     __shared__ __attribute__((aligned(16))) uint16_t kt[kPage * kPitch];
     __shared__ __attribute__((aligned(16))) uint16_t vt[kPage * kPitch];
     __shared__ int32_t sh_page[1];  // page index
@@ -370,8 +371,13 @@ __global__ void __launch_bounds__(256) append_step_kernel(AppendArgs a)
         return base + (((int64_t)b * a.max_new + (p - s_old)) * a.n_kv + h) * D;
     };
 
-    // ---- transformed new keys -> kn (row t: new token t)
+    // ---- transformed new keys -> kn (row t: new token t), values -> vn
     if (nn > 0) {
+        constexpr int kVec = D / 8;
+        static_assert(kStepMax * kVec <= 256, "one 16-byte piece of a value row per thread");
+        const int tv = tid / kVec, cv = tid % kVec;
+        uint4 vv = {0u, 0u, 0u, 0u};
+        if (tv < nn) vv = *reinterpret_cast<const uint4 *>(new_row(a.v_new, s_old + tv) + 8 * cv);
         const int j = lane >> 4, n = lane & 15;
         KeyTile<D, kNtW> xf;
         xf.load(a.tk, h, wave * kNtW, lane);
@@ -414,22 +420,30 @@ __global__ void __launch_bounds__(256) append_step_kernel(AppendArgs a)
                 }
             }
         }
+        if (tv < nn) *reinterpret_cast<uint4 *>(vn + tv * kPitch + 8 * cv) = vv;
     }
     __syncthreads();
 
     // ---- quantise [start_old, q_new), one page at a time
     if (start_old < q_new)
-        flush_range<D, BITS, true>(a, b, h, start_old, q_new, s_old, kn, kt, vt, sh_page, tid);
+        flush_range<D, BITS, true>(a, b, h, start_old, q_new, s_old, kn, vn, kt, vt, sh_page, tid);
 
     // ---- new tokens that stay bf16: sink, or the ring at or after q_new
-    for (int t = 0; t < nn; ++t) {
-        const int32_t p = s_old + t;
-        if (!(p < a.s_sink || p >= q_new)) continue;
-        const int32_t slot = p < a.s_sink ? p : ring_slot(p, a.s_sink, ring);
-        if (tid < D / 8)
-            *reinterpret_cast<uint4 *>(a.win_k + (head_win + slot) * D + 8 * tid) =
-                *reinterpret_cast<const uint4 *>(kn + t * kPitch + 8 * tid);
-        if (tid < D) a.win_v[(head_win * D) + (int64_t)tid * a.win_slots + slot] = new_row(a.v_new, p)[tid];
+    // (keys 16 bytes a thread; values channel-major, 16 threads the rows of a
+    // channel)
+    auto stays = [&](int32_t p) { return p < a.s_sink || p >= q_new; };
+    auto slot_of = [&](int32_t p) { return p < a.s_sink ? p : ring_slot(p, a.s_sink, ring); };
+    constexpr int kVec = D / 8;
+    if (const int t = tid / kVec, cv = tid % kVec; t < nn && stays(s_old + t))
+        *reinterpret_cast<uint4 *>(a.win_k + (head_win + slot_of(s_old + t)) * D + 8 * cv) =
+            *reinterpret_cast<const uint4 *>(kn + t * kPitch + 8 * cv);
+    if (const int t = tid % kStepMax; t < nn && stays(s_old + t)) {
+        uint16_t *dst = a.win_v + head_win * D + slot_of(s_old + t);
+#pragma unroll
+        for (int i = 0; i < D * kStepMax / 256; ++i) {
+            const int ch = tid / kStepMax + (256 / kStepMax) * i;
+            dst[(int64_t)ch * a.win_slots] = vn[t * kPitch + ch];
+        }
     }
     commit_finish(a, b, arrived, s_new, q_new, tid);
 }
@@ -451,9 +465,9 @@ static hipError_t launch_append_step(const AppendArgs &a, dim3 grid, hipStream_t
 
 // ------------------------------------------------------------------ step
 
-// Second launch of wushkv_decode_step.  Workgroups x < n_q merge the
-// attention splits of query head x of sequence y (as the decode combine
-// does); the n_kv after them then finish Alg. 2 for kv head x - n_q of
+// Second launch of wushkv_decode_step.  The first merge_wgs workgroups of
+// sequence y merge the attention splits of its query heads (as the decode
+// combine does); the n_kv after them then finish Alg. 2 for one kv head of
 // sequence y after its attention: the positions that left the recent window
 // are quantised from the ring (steps 7-11), and the last of a sequence's
 // workgroups advances its counters.
@@ -461,6 +475,8 @@ struct FinishArgs {
     const float *part;  // [batch][n_kv][n_splits][G][D + 2]
     float *out;         // [batch][n_kv G][D]
     int32_t G, n_splits;
+    int32_t merge_wgs;  // workgroups that merge, per sequence: n_q, or a quarter
+    bool merge_one;     // a wave to a row (merge_by_one)
 };
 
 template <int D, int BITS>
@@ -469,26 +485,30 @@ __global__ void __launch_bounds__(256) step_finish_kernel(AppendArgs a, FinishAr
     constexpr int kPitch = D + 8;
     __shared__ __attribute__((aligned(16))) uint16_t kt[kPage * kPitch];
     __shared__ __attribute__((aligned(16))) uint16_t vt[kPage * kPitch];
-    __shared__ float fw[kMaxSplits];
-    __shared__ float red[D];
+    __shared__ MergeLds<D> merge;
     __shared__ int32_t sh[4];  // page index, the counters (read_counters)
     const int tid = threadIdx.x, b = blockIdx.y;
     const int n_q = a.n_kv * f.G;
-    if ((int)blockIdx.x < n_q) {
-        const int qh = blockIdx.x, h = qh / f.G, g = qh % f.G;
+    if ((int)blockIdx.x < f.merge_wgs) {
+        // one query head, or (many rows) one a wave
+        const int qh = f.merge_one ? 4 * (int)blockIdx.x + (tid >> 6) : (int)blockIdx.x;
+        if (qh >= n_q) return;
+        const int h = qh / f.G, g = qh % f.G;
         const int64_t stride = (int64_t)f.G * (D + 2);
         const float *pp = f.part + ((int64_t)b * a.n_kv + h) * f.n_splits * stride + g * (D + 2);
-        merge_splits<D>(pp, stride, f.n_splits, f.out + ((int64_t)b * n_q + qh) * D, tid, fw, red);
+        float *dst = f.out + ((int64_t)b * n_q + qh) * D;
+        if (f.merge_one) merge_splits<D, 1>(pp, stride, f.n_splits, dst, tid, merge);
+        else merge_splits<D, 4>(pp, stride, f.n_splits, dst, tid, merge);
         return;
     }
-    const int h = (int)blockIdx.x - n_q;
+    const int h = (int)blockIdx.x - f.merge_wgs;
     const SeqCounters cnt = read_counters(a, b, 1, sh + 1, tid);
     const int32_t s_old = cnt.s_old, q_old = cnt.q_old, nn = cnt.nn;
     const int32_t s_new = s_old + nn;
     const int32_t q_new = next_quant_end(s_new, q_old, a.s_sink, a.s_keep, a.s_flush);
     const int32_t arrived = commit_arrive(a, b, s_old, q_old, nn, tid);
     const int32_t start = q_old > a.s_sink ? q_old : a.s_sink;
-    if (start < q_new) flush_range<D, BITS, false>(a, b, h, start, q_new, s_new, kt, kt, vt, sh, tid);
+    if (start < q_new) flush_range<D, BITS, false>(a, b, h, start, q_new, s_new, kt, vt, kt, vt, sh, tid);
     commit_finish(a, b, arrived, s_new, q_new, tid);
 }
 
@@ -669,8 +689,10 @@ int wushkv_step_finish(const wushkv_cache *c, const int32_t *n_new, const float 
     a.n_new = n_new;
     a.max_new = 1;
     a.arrivals = c->n_kv_heads;  // the flush workgroups of a sequence
-    FinishArgs f{part, out, G, n_splits};
-    const dim3 grid((unsigned)(c->n_kv_heads * G + c->n_kv_heads), (unsigned)c->batch);
+    const int32_t n_q = c->n_kv_heads * G;
+    const bool one = merge_by_one((int64_t)n_q * c->batch);
+    FinishArgs f{part, out, G, n_splits, one ? (n_q + 3) / 4 : n_q, one};
+    const dim3 grid((unsigned)(f.merge_wgs + c->n_kv_heads), (unsigned)c->batch);
     const int key = c->head_dim * 10 + storage_bits(c->bits);
     switch (key) {
         case 1282: launch("step_finish_kernel", step_finish_kernel<128, 2>, grid, dim3(256), s, a, f); break;

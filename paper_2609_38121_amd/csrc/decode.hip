@@ -13,7 +13,8 @@
 //                          head to one XCD.  q~ is scaled by sm_scale log2(e)
 //                          so that the softmax runs in base 2, and comes with
 //                          the form the quantised-key product consumes: q~ in
-//                          24-bit fixed point as six fp8 digit "limbs" with
+//                          24-bit fixed point as digit "limbs" (five fp6
+//                          ones with 2-bit keys, six fp8 ones otherwise) with
 //                          one power-of-two scale each, and sum(q~).
 //                          Workgroups 0 .. n_page_splits - 1 scan the
 //                          quantised pages, each wave a contiguous run; the
@@ -30,8 +31,8 @@
 // Quantised pages.  A stored key is k = s c + z per token, so
 //   q~ . k = s (q~ . c) + z sum(q~).
 // q~ . c comes from one 16x16x128 scaled matrix instruction per 16 tokens:
-// (two of them: limbs 0-3, then limbs 4-5) the rows are (query head, limb)
-// pairs of fp8 limbs with their E8M0 scales,
+// (two of them: limbs 0-3, then the others) the rows are (query head, limb)
+// pairs of the digit limbs with their E8M0 scales,
 // the columns are tokens whose 2-bit codes read as fp4 e2m1 (a code c in the
 // low two bits of a nibble is the value c / 2, exactly) or whose 4-bit codes
 // read as fp8 e4m3 (c in the low nibble of a byte is c 2^-9); a column scale
@@ -58,7 +59,19 @@
 namespace wushkv {
 
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr int kLimbs = 6;
+// Digit limbs of a query row (form_limbs): with 2-bit keys five base-32
+// digits as fp6 e2m3 numbers, with 4-bit keys six base-16 digits as fp8 e4m3
+// numbers.  Each limb takes 128 bytes; a row has room for six of either.
+constexpr int kLimbRoom = 6;
+template <int BITS>
+struct Limbs {
+    static constexpr int kCount = BITS == 2 ? 5 : 6;
+    static constexpr int kDigitBits = BITS == 2 ? 5 : 4;
+    static constexpr int kFmt = BITS == 2 ? 2 : 0;    // fp6 e2m3 or fp8 e4m3
+    static constexpr int kUnit = BITS == 2 ? 3 : 0;   // log2 of the integer a digit's code 1 stands for
+    // the largest N whose balanced digits (from -base/2 to base/2 - 1) fit
+    static constexpr float kNMax = BITS == 2 ? 16236015.0f : 7829367.0f;
+};
 
 typedef __attribute__((ext_vector_type(8))) int i32x8;
 
@@ -114,23 +127,6 @@ __device__ __forceinline__ int32_t chunk_tokens(const int32_t *n_tok, int32_t ma
 
 __device__ __forceinline__ float fexp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// Byte position, inside a limb's 128 operand bytes, of query channel ch: the
-// A operand lane group j' element i' of the scaled product meets the key
-// operand at the position the key codes' format dictates.  With fp4 keys
-// (2-bit) the fp8 element (j', i') meets fp4 lane group 2 (i' / 16) + j' / 2,
-// element 16 (j' % 2) + i' % 16, and the key codes put channel 32 j + i at
-// fp4 element (j, i); with fp8 keys (4-bit) elements meet one to one.
-template <int BITS>
-__host__ __device__ constexpr int limb_pos(int ch)
-{
-    if (BITS == 4) return ch;
-    const int j = ch >> 5, i = ch & 31;  // key lane group and element
-    // solve 2 (i' / 16) + j' / 2 = j and 16 (j' % 2) + i' % 16 = i
-    const int jp = 2 * (j & 1) + (i >> 4);
-    const int ip = 16 * (j >> 1) + (i & 15);
-    return 32 * jp + ip;
-}
-
 // ------------------------------------------------------------------ q~
 
 // LDS of a workgroup's query rows.  One region holds, in turn, the raw bf16
@@ -141,9 +137,9 @@ struct QueryLds {
     // the raw queries' row pitch in bf16 elements: rows 16 bytes apart in
     // the LDS banks, so that a column read across rows does not conflict
     static constexpr int kQPitch = D + 8;
-    static constexpr int kRegion = G * D * 4 > G * kLimbs * 128 ? G * D * 4 : G * kLimbs * 128;
+    static constexpr int kRegion = G * D * 4 > G * kLimbRoom * 128 ? G * D * 4 : G * kLimbRoom * 128;
     static constexpr int kAux = kRegion;  // uint32 [G][4]: limb scales (E8M0 bytes, limbs
-                                          // 0-3 then 4-5), sum(q~) (fp32 bits), unused
+                                          // 0-3 then the rest), sum(q~) (fp32 bits), unused
     static constexpr int kBytes = kRegion + G * 16;
 };
 
@@ -152,24 +148,23 @@ struct QueryLds {
 // (wave w covers columns D/4 w .. D/4 w + D/4 - 1 as kQuads groups of four;
 // lane (cq, part), cq = lane % kQuads, reads columns D/4 w + 4 cq .. + 3 of
 // rows part kRr .. part kRr + kRr - 1, one 16-byte load per row) and its
-// share of the raw queries (elements tid + 256 k of the G x D rows; rows of
+// share of the raw queries (elements tid + NT k of the G x D rows; rows of
 // tokens beyond a sequence's chunk are zero).
-template <int D, int G>
+template <int D, int G, int NT = 256>
 struct QueryIn {
     static constexpr int kQuads = D / 16;       // column quads per wave: 8 or 4
     static constexpr int kParts = 64 / kQuads;  // row parts per wave: 8 or 16
     static constexpr int kRr = D / kParts;      // rows per part: 16 or 4
-    static constexpr int kPer = (G * D + 255) / 256;
+    static constexpr int kPer = (G * D + NT - 1) / NT;
     f32x4 t[kRr];
     uint16_t q[kPer];
-    __device__ __forceinline__ void load(const DecodeArgs &a, int b, int tg, int h, int32_t S, int tid)
+    __device__ __forceinline__ void load_t(const DecodeArgs &a, int h, int tid)
     {
         const int lane = tid & 63, wave = tid >> 6;
         const float *T = a.tinv + (int64_t)h * D * D + (int64_t)(lane / kQuads) * kRr * D +
                          (D / 4) * wave + 4 * (lane % kQuads);
 #pragma unroll
         for (int r = 0; r < kRr; ++r) t[r] = *reinterpret_cast<const f32x4 *>(T + (int64_t)r * D);
-        load_q(a, b, tg, h, S, tid);
     }
     // the raw queries only
     __device__ __forceinline__ void load_q(const DecodeArgs &a, int b, int tg, int h, int32_t S, int tid)
@@ -180,7 +175,7 @@ struct QueryIn {
         const int32_t nb = decode ? 1 : chunk_tokens(a.n_tok, a.max_tok, b, S);
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
-            const int i = tid + 256 * k;
+            const int i = tid + NT * k;
             int64_t at = -1;
             if (i < G * D) {
                 if (decode) {
@@ -200,14 +195,14 @@ struct QueryIn {
 };
 
 // The raw queries into the region R (no barrier).
-template <int D, int G>
-__device__ __forceinline__ void stage_queries(const QueryIn<D, G> &in, uint8_t *R, int tid)
+template <int D, int G, int NT>
+__device__ __forceinline__ void stage_queries(const QueryIn<D, G, NT> &in, uint8_t *R, int tid)
 {
     uint16_t *qs = reinterpret_cast<uint16_t *>(R);  // bf16 [G][kQPitch]
     constexpr int kP = QueryLds<D, G>::kQPitch;
 #pragma unroll
-    for (int k = 0; k < QueryIn<D, G>::kPer; ++k) {
-        const int i = tid + 256 * k;
+    for (int k = 0; k < QueryIn<D, G, NT>::kPer; ++k) {
+        const int i = tid + NT * k;
         if (i < G * D) qs[(i / D) * kP + i % D] = in.q[k];
     }
 }
@@ -215,8 +210,8 @@ __device__ __forceinline__ void stage_queries(const QueryIn<D, G> &in, uint8_t *
 // q~ = q^T T^{-1} for the workgroup's G query rows (Alg. 2 step 3, Eq. (3)),
 // scaled by sm_scale log2(e), over the staged queries in R (QueryLds).  Each
 // lane forms its columns' partial products over its rows from the T^{-1}
-// entries it loaded (in); the row parts of a column are summed by lane
-// exchanges in a fixed order, so every workgroup of a (sequence, kv head)
+// entries it loaded (in); the row parts of a column are summed across lanes
+// in a fixed order, so every workgroup of a (sequence, kv head)
 // forms the same q~.  Every thread of the workgroup calls it after
 // stage_queries; it starts and ends with a barrier.
 template <int D, int G>
@@ -254,11 +249,14 @@ __device__ void form_qt(const DecodeArgs &a, const QueryIn<D, G> &in, uint8_t *R
         }
     // the row parts of the wave's columns: lanes cq + kQuads m
 #pragma unroll
-    for (int off = C::kQuads; off < 64; off <<= 1)
+    for (int g = 0; g < G; ++g)
 #pragma unroll
-        for (int g = 0; g < G; ++g)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) acc[g][c] += __shfl_xor(acc[g][c], off);
+        for (int c = 0; c < 4; ++c) {
+            float x = acc[g][c];
+            x += dpp<0x128>(x);                               // lane ^ 8
+            if constexpr (C::kQuads == 4) x += dpp<0x124>(x);  // and the other two of the row
+            acc[g][c] = add32(add16(x));
+        }
     __syncthreads();  // the raw queries are read
     float *qt = reinterpret_cast<float *>(R);
     if (lane < C::kQuads) {
@@ -270,30 +268,34 @@ __device__ void form_qt(const DecodeArgs &a, const QueryIn<D, G> &in, uint8_t *R
     __syncthreads();
 }
 
+// Waves of the query-row kernels: one per 16 output columns (at d = 128 each
+// wave then has half the T^{-1} reads, products and limbs that four waves would
+// have: 8.5 instead of 10.2 us for the 16 rows of a chunk's token groups; the
+// four rows of a decode take the same 8.6 us either way).
+template <int D>
+constexpr int kQtWaves = D / 16;
+
 // The T^{-1} entries lane l of wave w supplies to form_qt_mfma: column
-// D/4 w + 16 t + l % 16 at rows 4 st + l / 16.  Loaded on their own so that
-// a kernel can request them together with the raw queries (one round trip).
+// 16 w + l % 16 at rows 4 st + l / 16.  Loaded on their own so that a kernel
+// can request them together with the raw queries (one round trip).
 template <int D>
 struct TColumns {
-    static constexpr int kTiles = D / 64;  // 16-column tiles per wave
     static constexpr int kSteps = D / 4;   // k steps of 4
-    float bv[kTiles][kSteps];
+    float bv[kSteps];
     __device__ __forceinline__ void load(const DecodeArgs &a, int h, int tid)
     {
         const int lane = tid & 63, wave = tid >> 6;
-        const float *T = a.tinv + (int64_t)h * D * D + (D / 4) * wave + (lane & 15);
+        const float *T = a.tinv + (int64_t)h * D * D + 16 * wave + (lane & 15);
 #pragma unroll
-        for (int t = 0; t < kTiles; ++t)
-#pragma unroll
-            for (int st = 0; st < kSteps; ++st) bv[t][st] = T[(int64_t)(4 * st + (lane >> 4)) * D + 16 * t];
+        for (int st = 0; st < kSteps; ++st) bv[st] = T[(int64_t)(4 * st + (lane >> 4)) * D];
     }
 };
 
 // form_qt on the fp32 matrix instructions, for decode_qt_kernel (which has
 // no pages to overlap and is bound by the products): q~ = q^T T^{-1} as a
 // (16 x D) x (D x D) product of 16x16x4 fp32 tiles, the G query rows padded
-// to 16 with zeros.  Wave w takes the output columns D/4 w .. D/4 w + D/4 - 1
-// (D/64 tiles of 16); lane l supplies A = q[l % 16][k0 + l / 16] and
+// to 16 with zeros.  Wave w takes the output columns 16 w .. 16 w + 15; lane
+// l supplies A = q[l % 16][k0 + l / 16] and
 // B = T^{-1}[k0 + l / 16][n0 + l % 16] and holds the result rows
 // 4 (l / 16) .. + 3 of column n0 + l % 16.  The T^{-1} column entries of
 // all steps come loaded in tc.  Same contract as form_qt (q~ scaled,
@@ -302,115 +304,142 @@ struct TColumns {
 template <int D, int G>
 __device__ void form_qt_mfma(const DecodeArgs &a, const TColumns<D> &tc, uint8_t *R, int tid)
 {
-    constexpr int kTiles = TColumns<D>::kTiles;
     constexpr int kSteps = TColumns<D>::kSteps;
     const uint16_t *qs = reinterpret_cast<const uint16_t *>(R);
     const int lane = tid & 63, wave = tid >> 6;
     const int m = lane & 15, kk = lane >> 4;
-    const auto &bv = tc.bv;
     __syncthreads();  // the staged queries
-    f32x4 acc[kTiles];
-#pragma unroll
-    for (int t = 0; t < kTiles; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // (two sums, so that a product need not wait for the one before it)
+    f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
     for (int st = 0; st < kSteps; ++st) {
         const float av = m < G ? bf16_bits_to_f32(qs[m * QueryLds<D, G>::kQPitch + 4 * st + kk]) : 0.0f;
-#pragma unroll
-        for (int t = 0; t < kTiles; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv[t][st], acc[t], 0, 0, 0);
+        acc[st & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, tc.bv[st], acc[st & 1], 0, 0, 0);
     }
     __syncthreads();  // the raw queries are read
     float *qt = reinterpret_cast<float *>(R);
 #pragma unroll
-    for (int t = 0; t < kTiles; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row = 4 * kk + i;
-            if (row < G) qt[row * D + (D / 4) * wave + 16 * t + m] = acc[t][i] * a.scale;
-        }
+    for (int i = 0; i < 4; ++i) {
+        const int row = 4 * kk + i;
+        if (row < G) qt[row * D + 16 * wave + m] = (acc[0][i] + acc[1][i]) * a.scale;
+    }
     __syncthreads();
 }
 
 // Rewrites q~ in R (form_qt) as the operands of the quantised-key product:
 // one wave per query head writes q~ in fixed point, N = rne(q~ 2^F) with F
-// the largest exponent that keeps |N| <= 7829367, as six balanced base-16
-// digits d_l in [-8, 7] (N = sum_l d_l 16^(5 - l)).  Each digit is an fp8
-// integer and limb l carries the E8M0 scale 16^(5 - l) 2^-F, so every
-// product the matrix instruction forms is an integer times a power of two:
-// its block sums, which it does not accumulate at full fp32 precision in
-// general, are exact.  Also sum(q~) per head.  Every thread of the
+// the largest exponent that keeps |N| <= kNMax, as balanced digits (N =
+// sum_l d_l base^(kCount - 1 - l)).  Each digit is an integer of its number
+// format and limb l carries the E8M0 scale base^(kCount - 1 - l) 2^-F, so
+// every product the matrix instruction forms is an integer times a power of
+// two: its block sums, which it does not accumulate at full fp32 precision
+// in general, are exact.  Also sum(q~) per head.  Every thread of the
 // workgroup calls it; it ends with a barrier.
-template <int D, int BITS, int G>
+//
+// With 2-bit (fp4) keys the digits are five base-32 ones in fp6: the
+// products of fp6 with fp4 operands run at twice the rate of those with an
+// fp8 one (9.2 against 17 ns on one SIMD), five limbs hold a bit more than
+// six base-16 ones, and an operand takes six registers instead of eight.
+// With 4-bit (fp8) keys every product runs at the fp8 rate, so the digits
+// are six base-16 ones in fp8.
+// Operand order: lane group j of the instruction holds channels 32 j ..
+// 32 j + 31 in its 32 bytes of a limb, one byte each (fp8) or six bits each
+// in the first 24 (fp6).
+template <int D, int BITS, int G, int NW = 4>
 __device__ void form_limbs(uint8_t *R, int tid)
 {
     using Q = QueryLds<D, G>;
     const int lane = tid & 63, wave = tid >> 6;
     const float *qt = reinterpret_cast<const float *>(R);
-    // wave w handles query heads w, w + 4; the rows are read before the
+    // wave w handles query heads w, w + NW, ..; the rows are read before the
     // region is rewritten
     constexpr int kPer = D / 64;  // channels per lane
-    constexpr int kMine = (G + 3) / 4;
+    constexpr int kMine = (G + NW - 1) / NW;
     float r[kMine][kPer];
 #pragma unroll
     for (int k = 0; k < kMine; ++k)
 #pragma unroll
         for (int e = 0; e < kPer; ++e)
-            r[k][e] = (wave + 4 * k < G) ? qt[(wave + 4 * k) * D + 64 * e + lane] : 0.0f;
+            r[k][e] = (wave + NW * k < G) ? qt[(wave + NW * k) * D + 64 * e + lane] : 0.0f;
     __syncthreads();
     uint8_t *qlimb = R;
     uint32_t *qaux = reinterpret_cast<uint32_t *>(R + Q::kAux);
 #pragma unroll
     for (int k = 0; k < kMine; ++k) {
-        const int g = wave + 4 * k;
+        const int g = wave + NW * k;
         if (g >= G) break;
         float zs = 0.0f;
 #pragma unroll
         for (int e = 0; e < kPer; ++e) zs += r[k][e];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) zs += __shfl_xor(zs, off);
-        uint8_t *out = qlimb + g * (kLimbs * 128);
+        zs = wave_sum(zs);
+        uint8_t *out = qlimb + g * (kLimbRoom * 128);
         float mx = 0.0f;
 #pragma unroll
         for (int e = 0; e < kPer; ++e) mx = fmaxf(mx, fabsf(r[k][e]));
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-        // fixed point N = rne(q~ 2^F) with |N| <= 7829367 (< 2^23, exact
-        // in fp32), the largest value six balanced base-16 digits reach
-        constexpr float kNMax = 7829367.0f;
+        mx = wave_max(mx);
+        // fixed point N = rne(q~ 2^F), exact in fp32 (|N| < 2^24)
+        using LB = Limbs<BITS>;
         int F = 0;
         if (mx > 0.0f) {
             int ex;
-            (void)frexpf(kNMax / mx, &ex);
+            (void)frexpf(LB::kNMax / mx, &ex);
             F = ex - 1;
-            if (ldexpf(mx, F) > kNMax) F -= 1;
-            if (ldexpf(mx, F + 1) <= kNMax) F += 1;
+            if (ldexpf(mx, F) > LB::kNMax) F -= 1;
+            if (ldexpf(mx, F + 1) <= LB::kNMax) F += 1;
             F = F < -100 ? -100 : (F > 100 ? 100 : F);
         }
         uint32_t scales[2] = {0u, 0u};
 #pragma unroll
-        for (int l = 0; l < kLimbs; ++l)
-            scales[l >> 2] |= (uint32_t)(127 + 4 * (kLimbs - 1 - l) - F) << (8 * (l & 3));
+        for (int l = 0; l < LB::kCount; ++l)
+            scales[l >> 2] |= (uint32_t)(127 + LB::kUnit + LB::kDigitBits * (LB::kCount - 1 - l) - F) << (8 * (l & 3));
+        constexpr int kHalfBase = 1 << (LB::kDigitBits - 1);
 #pragma unroll
         for (int e = 0; e < kPer; ++e) {
             const int ch = 64 * e + lane;
             int N = (int)rintf(ldexpf(r[k][e], F));
 #pragma unroll
-            for (int l = kLimbs - 1; l >= 0; --l) {
-                const int d = ((N + 8) & 15) - 8;  // balanced digit
-                N = (N - d) >> 4;
-                // fp8 e4m3 of the integer d: exponent and top mantissa bits
-                // of its fp32 form
-                const uint32_t fb = __float_as_uint((float)(d < 0 ? -d : d));
-                const uint32_t code = (d == 0 ? 0u : ((((fb >> 23) - 120u) << 3) | ((fb >> 20) & 7u))) |
-                                      (d < 0 ? 0x80u : 0u);
-                out[l * 128 + limb_pos<BITS>(ch)] = (uint8_t)code;
+            for (int l = LB::kCount - 1; l >= 0; --l) {
+                const int d = ((N + kHalfBase) & (2 * kHalfBase - 1)) - kHalfBase;  // balanced digit
+                N = (N - d) >> LB::kDigitBits;
+                const uint32_t mag = (uint32_t)(d < 0 ? -d : d);
+                uint32_t code;
+                if constexpr (BITS == 2) {
+                    // fp6 e2m3 of d / 8: up to 16 the code is the integer itself
+                    code = mag | (d < 0 ? 0x20u : 0u);
+                } else {
+                    // fp8 e4m3 of the integer d: exponent and top mantissa bits
+                    // of its fp32 form
+                    const uint32_t fb = __float_as_uint((float)mag);
+                    code = (d == 0 ? 0u : ((((fb >> 23) - 120u) << 3) | ((fb >> 20) & 7u))) | (d < 0 ? 0x80u : 0u);
+                }
+                out[l * 128 + ch] = (uint8_t)code;
             }
         }
         if (D == 64) {
-            // operand positions no channel maps to are zero: with fp4 keys
-            // the elements 16 .. 31 of each lane group, with fp8 keys 64 ..
-            for (int l = 0; l < kLimbs; ++l)
-                for (int p = lane; p < 128; p += 64)
-                    if (BITS == 2 ? (p & 16) != 0 : p >= 64) out[l * 128 + p] = 0;
+            // channels 64 .. 127 of the operands: none, zero
+            for (int l = 0; l < LB::kCount; ++l) out[l * 128 + 64 + lane] = 0;
+        }
+        if constexpr (BITS == 2) {
+            // the codes, a byte each so far, packed to six bits: lane (limb,
+            // c) takes the 16 codes of channels 16 c ..  (this wave wrote
+            // them and reads them all before it writes over any)
+            __builtin_amdgcn_wave_barrier();
+            const int l = lane >> 3, c = lane & 7;
+            const bool mine = l < LB::kCount;
+            uint32_t p[4] = {0u, 0u, 0u, 0u};
+            if (mine) {
+                const u32x4 w = *reinterpret_cast<const u32x4 *>(out + l * 128 + 16 * c);
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    p[q] = (w[q] & 0x3Fu) | ((w[q] >> 2) & 0xFC0u) | ((w[q] >> 4) & 0x3F000u) | ((w[q] >> 6) & 0xFC0000u);
+            }
+            __builtin_amdgcn_wave_barrier();
+            if (mine) {
+                uint32_t *dst = reinterpret_cast<uint32_t *>(out + l * 128 + 32 * (c >> 1) + 12 * (c & 1));
+                dst[0] = p[0] | (p[1] << 24);
+                dst[1] = (p[1] >> 8) | (p[2] << 16);
+                dst[2] = (p[2] >> 16) | (p[3] << 8);
+            }
         }
         if (lane == 0) {
             qaux[4 * g] = scales[0];
@@ -428,7 +457,7 @@ __device__ void form_limbs(uint8_t *R, int tid)
 // then run in several rounds, and each forming q~ itself would read T^{-1}
 // from L2 once per workgroup.
 template <int D, int BITS, int G>
-__global__ void __launch_bounds__(256) decode_qt_kernel(DecodeArgs a)
+__global__ void __launch_bounds__(64 * kQtWaves<D>) decode_qt_kernel(DecodeArgs a)
 {
     using Q = QueryLds<D, G>;
     __shared__ __attribute__((aligned(16))) uint8_t R[Q::kBytes];
@@ -438,16 +467,17 @@ __global__ void __launch_bounds__(256) decode_qt_kernel(DecodeArgs a)
     const int32_t S = (a.max_tok == 1 && a.n_tok == nullptr) ? 0 : a.seq_len[b];
     TColumns<D> tc;
     tc.load(a, h, tid);
-    QueryIn<D, G> in;
+    constexpr int NT = 64 * kQtWaves<D>;
+    QueryIn<D, G, NT> in;
     in.load_q(a, b, tg, h, S, tid);
-    stage_queries<D, G>(in, R, tid);
+    stage_queries(in, R, tid);
     form_qt_mfma<D, G>(a, tc, R, tid);
     const int64_t row0 = ((int64_t)bz * a.n_kv + h) * G;  // first (virtual) query head
-    for (int i = tid; i < G * D / 4; i += 256)
+    for (int i = tid; i < G * D / 4; i += NT)
         reinterpret_cast<f32x4 *>(a.qt + row0 * D)[i] = reinterpret_cast<const f32x4 *>(R)[i];
-    form_limbs<D, BITS, G>(R, tid);
-    for (int i = tid; i < G * kLimbs * 128 / 16; i += 256)
-        reinterpret_cast<u32x4 *>(a.qlimb + row0 * kLimbs * 128)[i] = reinterpret_cast<const u32x4 *>(R)[i];
+    form_limbs<D, BITS, G, kQtWaves<D>>(R, tid);
+    for (int i = tid; i < G * kLimbRoom * 128 / 16; i += NT)
+        reinterpret_cast<u32x4 *>(a.qlimb + row0 * kLimbRoom * 128)[i] = reinterpret_cast<const u32x4 *>(R)[i];
     if (tid < G * 4) a.qaux[row0 * 4 + tid] = reinterpret_cast<const uint32_t *>(R + Q::kAux)[tid];
 }
 
@@ -457,7 +487,7 @@ __global__ void __launch_bounds__(256) decode_qt_kernel(DecodeArgs a)
 // T^{-1} once per pair; each group's rows go where decode_qt_kernel puts
 // them.
 template <int BITS>
-__global__ void __launch_bounds__(256) chunk_qt_kernel(DecodeArgs a)
+__global__ void __launch_bounds__(64 * kQtWaves<128>) chunk_qt_kernel(DecodeArgs a)
 {
     constexpr int D = 128, G = 8, G2 = 16;
     using Q = QueryLds<D, G2>;
@@ -471,62 +501,28 @@ __global__ void __launch_bounds__(256) chunk_qt_kernel(DecodeArgs a)
     // group tg + v / 8, virtual head v % 8 of that group
     TColumns<D> tc;
     tc.load(a, h, tid);
-    QueryIn<D, G2> in;
+    constexpr int NT = 64 * kQtWaves<D>;
+    QueryIn<D, G2, NT> in;
     in.load_q(a, b, tg, h, S, tid);
-    stage_queries<D, G2>(in, R, tid);
+    stage_queries(in, R, tid);
     form_qt_mfma<D, G2>(a, tc, R, tid);
     const int n_mine = tg + 1 < a.n_groups ? 2 : 1;
     for (int e = 0; e < n_mine; ++e) {
         const int64_t row0 = (((int64_t)b * a.n_groups + tg + e) * a.n_kv + h) * G;
-        for (int i = tid; i < G * D / 4; i += 256)
+        for (int i = tid; i < G * D / 4; i += NT)
             reinterpret_cast<f32x4 *>(a.qt + row0 * D)[i] = reinterpret_cast<const f32x4 *>(R)[e * G * D / 4 + i];
     }
-    form_limbs<D, BITS, G2>(R, tid);
+    form_limbs<D, BITS, G2, kQtWaves<D>>(R, tid);
     for (int e = 0; e < n_mine; ++e) {
         const int64_t row0 = (((int64_t)b * a.n_groups + tg + e) * a.n_kv + h) * G;
-        for (int i = tid; i < G * kLimbs * 128 / 16; i += 256)
-            reinterpret_cast<u32x4 *>(a.qlimb + row0 * kLimbs * 128)[i] =
-                reinterpret_cast<const u32x4 *>(R)[e * G * kLimbs * 128 / 16 + i];
+        for (int i = tid; i < G * kLimbRoom * 128 / 16; i += NT)
+            reinterpret_cast<u32x4 *>(a.qlimb + row0 * kLimbRoom * 128)[i] =
+                reinterpret_cast<const u32x4 *>(R)[e * G * kLimbRoom * 128 / 16 + i];
         if (tid < G * 4) a.qaux[row0 * 4 + tid] = reinterpret_cast<const uint32_t *>(R + Q::kAux)[e * G * 4 + tid];
     }
 }
 
 // ------------------------------------------------------------------ main
-
-template <int CTRL>
-__device__ __forceinline__ float dpp(float x)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x),
-                                                                  CTRL, 0xF, 0xF, false));
-}
-// max / sum over the 16 lanes of a row (quad butterflies, then rotations).
-// The max is four DPP-operand maxima in one assembly block; each is preceded
-// by the two wait states a DPP read of a just-written register needs.  The
-// inputs are finite or -inf.
-__device__ __forceinline__ float row_max16(float x)
-{
-    float y;
-    asm volatile(
-        "s_nop 1\n\t"
-        "v_max_f32_dpp %0, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 1\n\t"
-        "v_max_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 1\n\t"
-        "v_max_f32_dpp %0, %0, %0 row_ror:4 row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 1\n\t"
-        "v_max_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0xf"
-        : "=&v"(y)
-        : "v"(x));
-    return y;
-}
-__device__ __forceinline__ float row_sum16(float x)
-{
-    x += dpp<0xB1>(x);
-    x += dpp<0x4E>(x);
-    x += dpp<0x124>(x);
-    x += dpp<0x128>(x);
-    return x;
-}
 
 __device__ __forceinline__ void __attribute__((address_space(3))) *lds_ptr(void *p)
 {
@@ -608,12 +604,13 @@ __device__ __forceinline__ void wait_vmcnt_at_most(int after)
     else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kMaxAhead * kDma) : "memory");
 }
 
-__device__ __forceinline__ f32x4 mfma_scaled(const i32x8 &a, const i32x8 &b, int fmt_b, int scale_a,
-                                             int scale_b, f32x4 c)
+// Query digits (fp6 with 2-bit keys, fp8 with 4-bit ones) times key codes
+// (fp4 or fp8).
+template <int BITS>
+__device__ __forceinline__ f32x4 mfma_scaled(const i32x8 &a, const i32x8 &b, int scale_a, int scale_b, f32x4 c)
 {
-    if (fmt_b == 4)
-        return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 0, 4, 0, scale_a, 0, scale_b);
-    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 0, 0, 0, scale_a, 0, scale_b);
+    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, Limbs<BITS>::kFmt, BITS == 2 ? 4 : 0, 0, scale_a,
+                                                            0, scale_b);
 }
 
 // LDS per wave: page stages (also the merge buffer) and the weight buffer.
@@ -622,7 +619,10 @@ struct MainLds {
     using L = Layout<D, BITS>;
     static constexpr int kStages = 2;
     static constexpr int kDma = (L::kPageBytes + 1023) / 1024;  // direct-to-LDS loads per page
-    static constexpr int kSlot = kDma * 1024;
+    // (the last load of a page is masked to the page's end, so slots are no
+    // longer than that: with 4-bit codes, d = 128 and eight heads the rounding
+    // to whole loads kept a second workgroup off the compute unit)
+    static constexpr int kSlot = (L::kPageBytes + 15) / 16 * 16;
     static constexpr int kStageBytes = kStages * kSlot > G * D * 4 ? kStages * kSlot : G * D * 4;
     // weight buffer: 2G rows of 64 tokens (fp16 or bf16; row part G + g
     // holds part `part` of head g), then a zero row.  The 144-byte pitch
@@ -633,11 +633,11 @@ struct MainLds {
     static constexpr int kWave = kStageBytes + kTBytes;
     // Workgroups a compute unit keeps resident, as the variants' register
     // counts allow (three waves per SIMD at most; fewer for the 4-bit and
-    // the eight-head ones: the 2-bit eight-head decode kernel at d = 128 and
-    // the 4-bit eight-head kernels at d = 64 are given two, and the
-    // registers of a third, so that their page loops do not spill); it only
-    // decides the query rows' placement.
-    static constexpr int kResident = D == 128 ? (BITS == 2 ? (G == 8 ? 2 : 3) : (G == 8 ? 1 : 2))
+    // the eight-head ones: the eight-head decode kernels at d = 128 and the
+    // 4-bit eight-head kernels at d = 64 are given two, and the registers of
+    // a third, so that their page loops do not spill); it only decides the
+    // query rows' placement.
+    static constexpr int kResident = D == 128 ? (BITS == 2 ? (G == 8 ? 2 : 3) : 2)
                                               : (BITS == 2 ? (G == 8 ? 3 : 4) : (G == 8 ? 2 : 3));
     // The query rows get LDS of their own when that keeps the residency:
     // the pages can then be in flight while the rows are formed.  Otherwise
@@ -700,7 +700,7 @@ __device__ void step_token(const DecodeArgs &a, int b, int h, int32_t slot, uint
 // HBM once per four token groups; grid z runs over (sequence, group of four
 // token groups) and every wave writes its own partials.
 template <int D, int BITS, int G, bool FORM, bool SHARE>
-__global__ void __launch_bounds__(256, ((D == 128 && BITS == 2 && G == 8 && !SHARE) || (D == 64 && BITS == 4 && G == 8)) ? 2 : 3)
+__global__ void __launch_bounds__(256, ((D == 128 && (BITS == 4 || (G == 8 && !SHARE))) || (D == 64 && BITS == 4 && G == 8)) ? 2 : 3)
 decode_main_kernel(DecodeArgs a)
 {
     static_assert(!(FORM && SHARE), "shared work items take q~ from decode_qt_kernel");
@@ -716,7 +716,6 @@ decode_main_kernel(DecodeArgs a)
     constexpr int kOpw = L::kOpsPerWord;
     constexpr int kHG = G > 4 ? 2 : 1;          // score products per 16 tokens
     constexpr int kRowsPerHead = G > 4 ? 2 : 4; // P V rows per head (pages): hi, lo, [zero, zero]
-    constexpr int kFmtB = BITS == 2 ? 4 : 0;    // fp4 or fp8 key codes
     constexpr int kScaleB = BITS == 2 ? 128 : 136;  // 2^1 or 2^9
 
     __shared__ __attribute__((aligned(16))) uint8_t lds[FORM ? M::kBytes : 4 * M::kWave];
@@ -740,6 +739,18 @@ decode_main_kernel(DecodeArgs a)
     constexpr int kTP = M::kTPitch;
     const uint32_t zero_row = lds_addr(tbuf + M::kTRows * kTP);
 
+    // What needs no counter is requested first: the T^{-1} entries and queries
+    // of q~, and the page-table entries of this wave's run (a run's share
+    // beyond the sequence's pages is not used)
+    const bool page_wg = split < a.n_page_splits;
+    const int upw = a.units_per_wave;
+    const int w0 = page_wg ? (SHARE ? split : split * 4 + wave) * upw : 0;
+    QueryIn<D, G> qin;
+    if constexpr (FORM) qin.load_t(a, h, tid);
+    int32_t tbl = -1;
+    if (page_wg && a.n_pages > 0 && lane < upw && w0 + lane < a.max_pages)
+        tbl = a.page_table[(int64_t)b * a.max_pages + w0 + lane];
+
     // fused step: the new token is position seq_len[b] and is attended to
     const int32_t s_old = a.seq_len[b];
     int32_t nn = a.n_new != nullptr ? a.n_new[b] : 0;
@@ -753,17 +764,8 @@ decode_main_kernel(DecodeArgs a)
     // per-wave results for the merge: o (unnormalised, relative to m), m, l
     float(*sC)[D] = reinterpret_cast<float(*)[D]>(stage);
 
-    // the page run of this wave and its page-table entries, then the T^{-1}
-    // entries of q~, all requested before any page
-    const bool page_wg = split < a.n_page_splits;
-    const int upw = a.units_per_wave;
-    const int w0 = page_wg ? (SHARE ? split : split * 4 + wave) * upw : 0;
     const int w1 = page_wg && rows_live ? min(w0 + upw, n_qpages) : 0;
-    int32_t tbl = -1;
-    if (w0 + lane < w1 && w0 + lane < a.max_pages)
-        tbl = a.page_table[(int64_t)b * a.max_pages + w0 + lane];
-    QueryIn<D, G> qin;
-    if constexpr (FORM) qin.load(a, b, tg, h, S, tid);
+    if constexpr (FORM) qin.load_q(a, b, tg, h, S, tid);
     using Q = QueryLds<D, G>;
     uint8_t *qrows = lds + M::kRowsAt;
     const int64_t row0 = ((int64_t)bz * a.n_kv + h) * G;  // first (virtual) query head
@@ -793,7 +795,7 @@ decode_main_kernel(DecodeArgs a)
             // run go in flight while q~ is formed.  Every load made so far
             // completes first, so that no later wait of the rows' arithmetic
             // can be held up by the pages (loads complete in issue order).
-            stage_queries<D, G>(qin, qrows, tid);
+            stage_queries(qin, qrows, tid);
             if (kEarly) {
                 // vmcnt(0) as the compiler's own wait: it then counts the
                 // rows' loads complete and sets no wait on them behind the pages
@@ -808,13 +810,15 @@ decode_main_kernel(DecodeArgs a)
             qlimb = qrows;
             qaux = reinterpret_cast<const uint32_t *>(qrows + Q::kAux);
         } else {
-            qlimb = a.qlimb + row0 * kLimbs * 128;
+            qlimb = a.qlimb + row0 * kLimbRoom * 128;
             qaux = a.qaux + row0 * 4;
         }
 
         // score A operands, two per head group: row m = 4 g' + r holds limb
-        // r (first) or limb 4 + r for r < 2 (second; rows r >= 2 zero) of
-        // head hd = g' (G <= 4) or 2 g' + hg (G = 8); heads >= G give zero rows
+        // r (first) or, in the last rows, the limbs from 4 on (second; the
+        // other rows zero) of head hd = g' (G <= 4) or 2 g' + hg (G = 8);
+        // heads >= G give zero rows
+        using LB = Limbs<BITS>;
         i32x8 qa[kHG][2];
         int qsc[kHG][2];
         float zs[kHG];  // sum(q~) of the head this lane's scores belong to
@@ -823,14 +827,14 @@ decode_main_kernel(DecodeArgs a)
             const int hd = G > 4 ? 2 * (n >> 2) + hg : (n >> 2);
 #pragma unroll
             for (int part = 0; part < 2; ++part) {
-                const int limb = 4 * part + (n & 3);
+                const int limb = part == 0 ? (n & 3) : LB::kCount - 4 + (n & 3);
                 u32x4 x0 = {0u, 0u, 0u, 0u}, x1 = x0;
                 qsc[hg][part] = 127;
-                if (hd < G && limb < kLimbs) {
-                    const uint8_t *src = qlimb + (hd * kLimbs + limb) * 128 + 32 * j;
+                if (hd < G && limb >= 4 * part) {
+                    const uint8_t *src = qlimb + (hd * kLimbRoom + limb) * 128 + 32 * j;
                     x0 = *reinterpret_cast<const u32x4 *>(src);
                     x1 = *reinterpret_cast<const u32x4 *>(src + 16);
-                    qsc[hg][part] = (qaux[4 * hd + part] >> (8 * (n & 3))) & 0xFFu;
+                    qsc[hg][part] = (qaux[4 * hd + part] >> (8 * (limb - 4 * part))) & 0xFFu;
                 }
                 qa[hg][part] = i32x8{(int)x0[0], (int)x0[1], (int)x0[2], (int)x0[3],
                                      (int)x1[0], (int)x1[1], (int)x1[2], (int)x1[3]};
@@ -940,20 +944,20 @@ decode_main_kernel(DecodeArgs a)
                                        (int)(w[3] & 0x0F0F0F0Fu), (int)((w[3] >> 4) & 0x0F0F0F0Fu)};
                     }
                 }
-                // limbs 4-5 (rows 4 g' + 0, 1 of the second product) are
-                // accumulated onto limbs 0-1 of the first, so each head's six
-                // limbs end up in its four rows
+                // the limbs from 4 on (the last rows of the second product)
+                // are accumulated onto the lowest ones of the first, so each
+                // head's limbs end up in its four rows
                 f32x4 c[kHG][4];
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
 #pragma unroll
                     for (int hg = 0; hg < kHG; ++hg)
-                        c[hg][t] = mfma_scaled(qa[hg][0], bop[t], kFmtB, qsc[hg][0], kScaleB, f32x4{0.f, 0.f, 0.f, 0.f});
+                        c[hg][t] = mfma_scaled<BITS>(qa[hg][0], bop[t], qsc[hg][0], kScaleB, f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
 #pragma unroll
                     for (int hg = 0; hg < kHG; ++hg)
-                        c[hg][t] = mfma_scaled(qa[hg][1], bop[t], kFmtB, qsc[hg][1], kScaleB, c[hg][t]);
+                        c[hg][t] = mfma_scaled<BITS>(qa[hg][1], bop[t], qsc[hg][1], kScaleB, c[hg][t]);
                 float lg[kHG][4];
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
@@ -1119,7 +1123,7 @@ decode_main_kernel(DecodeArgs a)
 
         const float *qtl;
         if constexpr (FORM) {
-            stage_queries<D, G>(qin, qrows, tid);
+            stage_queries(qin, qrows, tid);
             form_qt<D, G>(a, qin, qrows, tid);
             qtl = reinterpret_cast<const float *>(qrows);
         } else {
@@ -1345,10 +1349,10 @@ decode_main_kernel(DecodeArgs a)
 // unpacked once.  Pages stream through three LDS slots that the four waves
 // share (each wave loads its part of every page).  Per page:
 //   scores  wave w takes rows 16 w .. 16 w + 15: one scaled product per
-//           limb and 16 tokens, whose A rows are the 16 query rows' fp8
+//           limb and 16 tokens, whose A rows are the 16 query rows'
 //           digits of that limb (held in registers for the whole run, each
 //           row with its own E8M0 scale) and whose B columns are the fp4 /
-//           fp8 key codes, accumulated over the six limbs; lane (j, n) then
+//           fp8 key codes, accumulated over the limbs; lane (j, n) then
 //           holds rows 16 w + 4 j + r of tokens 4 n .. 4 n + 3, runs their
 //           online softmax and writes their weights (fp16 hi + lo) and
 //           rescale factors to LDS;
@@ -1381,13 +1385,16 @@ struct ChunkLds {
     static constexpr int kBytes = kSlotAt + kSlots * kSlot;
 };
 
-// One limb's scaled product: A = limb L of 16 query rows, whose E8M0 scale
-// is byte L % 4 of the lane's packed scale word (the instruction's byte
-// select), B = 16 tokens' key codes.
-template <int L, int FMT_B, int SCALE_B>
-__device__ __forceinline__ f32x4 limb_product(const i32x8 &a, const i32x8 &b, int scales, f32x4 c)
+// One limb's scaled products with four tiles of 16 tokens: A = limb L of 16
+// query rows, whose E8M0 scale is byte L % 4 of the lane's packed scale word
+// (the instruction's byte select), B = the tokens' key codes.
+template <int BITS, int L, int SCALE_B>
+__device__ __forceinline__ void limb_products(const i32x8 &a, const i32x8 (&b)[4], int scales, f32x4 (&c)[4])
 {
-    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 0, FMT_B, L % 4, scales, 0, SCALE_B);
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+        c[t] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b[t], c[t], Limbs<BITS>::kFmt, BITS == 2 ? 4 : 0,
+                                                                L % 4, scales, 0, SCALE_B);
 }
 
 template <int BITS>
@@ -1398,7 +1405,6 @@ __global__ void __launch_bounds__(256, 2) chunk_pages_kernel(DecodeArgs a)
     using C = ChunkLds<BITS>;
     constexpr int kDma = (L::kPageBytes + 1023) / 1024;  // direct-to-LDS loads per page
     constexpr int kNTw = L::kNTiles / 4;                  // channel tiles per wave
-    constexpr int kFmtB = BITS == 2 ? 4 : 0;
     constexpr int kScaleB = BITS == 2 ? 128 : 136;
     constexpr int kKX = L::kKWordsPerLane / 4;            // key chunks per lane
     constexpr int kOpw = L::kOpsPerWord;
@@ -1430,15 +1436,16 @@ __global__ void __launch_bounds__(256, 2) chunk_pages_kernel(DecodeArgs a)
         const int tg = tg0 + r64 / G;
         return tg < a.n_groups ? (((int64_t)b * a.n_groups + tg) * a.n_kv + h) * G + r64 % G : -1;
     };
-    i32x8 qa[kLimbs];
+    constexpr int kCount = Limbs<BITS>::kCount;
+    i32x8 qa[kCount];
     int sc03 = 0, sc45 = 0;
     {
         const int64_t row = row_of(16 * wave + n);
 #pragma unroll
-        for (int l = 0; l < kLimbs; ++l) {
+        for (int l = 0; l < kCount; ++l) {
             u32x4 x0 = {0u, 0u, 0u, 0u}, x1 = x0;
             if (row >= 0) {
-                const uint8_t *src = a.qlimb + row * (kLimbs * 128) + l * 128 + 32 * j;
+                const uint8_t *src = a.qlimb + row * (kLimbRoom * 128) + l * 128 + 32 * j;
                 x0 = *reinterpret_cast<const u32x4 *>(src);
                 x1 = *reinterpret_cast<const u32x4 *>(src + 16);
             }
@@ -1539,17 +1546,13 @@ __global__ void __launch_bounds__(256, 2) chunk_pages_kernel(DecodeArgs a)
             }
         }
 #pragma unroll
-        for (int t = 0; t < 4; ++t) c[t] = limb_product<0, kFmtB, kScaleB>(qa[0], bop[t], sc03, f32x4{0.f, 0.f, 0.f, 0.f});
-#pragma unroll
-        for (int t = 0; t < 4; ++t) c[t] = limb_product<1, kFmtB, kScaleB>(qa[1], bop[t], sc03, c[t]);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) c[t] = limb_product<2, kFmtB, kScaleB>(qa[2], bop[t], sc03, c[t]);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) c[t] = limb_product<3, kFmtB, kScaleB>(qa[3], bop[t], sc03, c[t]);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) c[t] = limb_product<4, kFmtB, kScaleB>(qa[4], bop[t], sc45, c[t]);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) c[t] = limb_product<5, kFmtB, kScaleB>(qa[5], bop[t], sc45, c[t]);
+        for (int t = 0; t < 4; ++t) c[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        limb_products<BITS, 0, kScaleB>(qa[0], bop, sc03, c);
+        limb_products<BITS, 1, kScaleB>(qa[1], bop, sc03, c);
+        limb_products<BITS, 2, kScaleB>(qa[2], bop, sc03, c);
+        limb_products<BITS, 3, kScaleB>(qa[3], bop, sc03, c);
+        limb_products<BITS, 4, kScaleB>(qa[4], bop, sc45, c);
+        if constexpr (kCount > 5) limb_products<BITS, 5, kScaleB>(qa[5], bop, sc45, c);
     };
     // the online softmax of page u over the products: the weights (fp16
     // hi + lo) and rescale factors of the wave's rows into LDS; tail: mask
@@ -1687,7 +1690,7 @@ __global__ void __launch_bounds__(256, 2) chunk_pages_kernel(DecodeArgs a)
                 pv(u - 1);
                 softmax(u, c, kp, vp, false, kPage);
 #pragma unroll
-                for (int i = 0; i < 24; ++i) {
+                for (int i = 0; i < 4 * kCount; ++i) {
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // a score product
                     __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);  // vector arithmetic
                 }
@@ -2053,21 +2056,18 @@ __global__ void __launch_bounds__(256, 1) chunk_window_kernel(DecodeArgs a, floa
 
 // ------------------------------------------------------------------ combine
 
-// One workgroup per (query head, sequence): the split maxima and weights go
-// through LDS, then every channel thread sums its column with the loads
-// unrolled so they are in flight together.
-template <int D>
-__global__ void __launch_bounds__(D) decode_combine_kernel(const float *part, float *out,
-                                                           int32_t n_kv, int32_t G,
-                                                           int32_t n_splits, DecodeArgs a)
+// One workgroup of NW waves per (query head, sequence).
+template <int D, int NW>
+__global__ void __launch_bounds__(64 * NW) decode_combine_kernel(const float *part, float *out,
+                                                                 int32_t n_kv, int32_t G,
+                                                                 int32_t n_splits, DecodeArgs a)
 {
-    __shared__ float fw[kMaxSplits];
-    __shared__ float red[D];
+    __shared__ MergeLds<D> lds;
     // virtual head qh = (h, v) of grid row bz = (b, token group tg): chunk
     // token tg tpg + v / g_real, query head h g_real + v % g_real
     const int qh = blockIdx.x, bz = blockIdx.y;
     const int h = qh / G, g = qh % G;
-    const int ch = threadIdx.x;
+    const int tid = threadIdx.x;
     float *dst;
     if (a.max_tok == 1 && a.n_tok == nullptr) {
         dst = out + ((int64_t)bz * n_kv * G + qh) * D;  // decode: row bz = b, head qh
@@ -2077,13 +2077,13 @@ __global__ void __launch_bounds__(D) decode_combine_kernel(const float *part, fl
         if (t >= a.max_tok) return;
         dst = out + (((int64_t)b * a.max_tok + t) * n_kv * a.g_real + h * a.g_real + g % a.g_real) * D;
         if (t >= chunk_tokens(a.n_tok, a.max_tok, b, a.seq_len[b])) {
-            dst[ch] = 0.0f;  // beyond this sequence's chunk
+            for (int ch = tid; ch < D; ch += 64 * NW) dst[ch] = 0.0f;  // beyond this sequence's chunk
             return;
         }
     }
     const int64_t stride = (int64_t)G * (D + 2);
     const float *pp = part + (((int64_t)bz * n_kv + h) * n_splits) * stride + g * (D + 2);
-    merge_splits<D>(pp, stride, n_splits, dst, ch, fw, red);
+    merge_splits<D, NW>(pp, stride, n_splits, dst, tid, lds);
 }
 
 // ------------------------------------------------------------------ host
@@ -2262,7 +2262,7 @@ static bool make_plan(const wushkv_cache *c, const RowShape &rs, int32_t max_seq
     p.n_page_splits = (int32_t)psplits;
     p.n_splits = (int32_t)splits;
     p.qt_bytes = ((size_t)rows_z * n_q * c->head_dim * 4 + 255) / 256 * 256;
-    p.limb_bytes = (size_t)rows_z * n_q * kLimbs * 128;
+    p.limb_bytes = (size_t)rows_z * n_q * kLimbRoom * 128;
     p.aux_bytes = ((size_t)rows_z * n_q * 16 + 255) / 256 * 256;
     p.part_bytes = (size_t)heads * splits * G * (c->head_dim + 2) * 4;
     return true;
@@ -2278,7 +2278,7 @@ static void launch_main(bool form, bool share, dim3 grid, unsigned rows_z, hipSt
         launch("decode_main_kernel", decode_main_kernel<D, BITS, G, true, false>, grid, dim3(256), s, a);
         return;
     }
-    launch("decode_qt_kernel", decode_qt_kernel<D, BITS, G>, dim3(grid.x, rows_z), dim3(256), s, a);
+    launch("decode_qt_kernel", decode_qt_kernel<D, BITS, G>, dim3(grid.x, rows_z), dim3(64 * kQtWaves<D>), s, a);
     if (share)
         launch("decode_main_kernel", decode_main_kernel<D, BITS, G, false, true>, grid, dim3(256), s, a);
     else
@@ -2424,10 +2424,10 @@ static int attend(const wushkv_cache *c, const uint16_t *q, const int32_t *n_tok
         const dim3 gw(c->n_kv_heads, 4 * blocks);
         const dim3 gq(c->n_kv_heads, (unsigned)(c->batch * ((rs.n_groups + 1) / 2)));
         if (key == 1282) {
-            launch("chunk_qt_kernel", chunk_qt_kernel<2>, gq, dim3(256), s, a);
+            launch("chunk_qt_kernel", chunk_qt_kernel<2>, gq, dim3(64 * kQtWaves<128>), s, a);
             if (p.n_page_splits > 0) launch("chunk_pages_kernel", chunk_pages_kernel<2>, gp, dim3(256), s, a);
         } else {
-            launch("chunk_qt_kernel", chunk_qt_kernel<4>, gq, dim3(256), s, a);
+            launch("chunk_qt_kernel", chunk_qt_kernel<4>, gq, dim3(64 * kQtWaves<128>), s, a);
             if (p.n_page_splits > 0) launch("chunk_pages_kernel", chunk_pages_kernel<4>, gp, dim3(256), s, a);
         }
         launch("chunk_window_kernel", chunk_window_kernel, gw, dim3(256), s, a, out);
@@ -2443,8 +2443,15 @@ static int attend(const wushkv_cache *c, const uint16_t *q, const int32_t *n_tok
         if (hipGetLastError() != hipSuccess) return WUSHKV_ELAUNCH;
         return wushkv_step_finish(c, step->n_new, part, out, G, p.n_splits, s);
     }
-    if (c->head_dim == 128) launch("decode_combine_kernel", decode_combine_kernel<128>, gc, dim3(128), s, (const float *)part, out, c->n_kv_heads, G, p.n_splits, a);
-    else launch("decode_combine_kernel", decode_combine_kernel<64>, gc, dim3(64), s, (const float *)part, out, c->n_kv_heads, G, p.n_splits, a);
+    auto combine = [&](auto kernel, int nw) {
+        launch("decode_combine_kernel", kernel, gc, dim3(64 * nw), s, (const float *)part, out, c->n_kv_heads, G,
+               p.n_splits, a);
+    };
+    const bool one = merge_by_one((int64_t)gc.x * gc.y);
+    if (c->head_dim == 128 && one) combine(decode_combine_kernel<128, 1>, 1);
+    else if (c->head_dim == 128) combine(decode_combine_kernel<128, kMergeWaves>, kMergeWaves);
+    else if (one) combine(decode_combine_kernel<64, 1>, 1);
+    else combine(decode_combine_kernel<64, kMergeWaves>, kMergeWaves);
     if (hipGetLastError() != hipSuccess) return WUSHKV_ELAUNCH;
     return WUSHKV_OK;
 }

@@ -431,51 +431,57 @@ __device__ __forceinline__ uint8_t *vcode_row(uint16_t *vt, int t)
     return reinterpret_cast<uint8_t *>(vt + t * (D + 8));
 }
 
-// Phase C of a tile: the value-code words, from the code bytes that phase
-// B left in the value rows (vcode_row).  full: every position of the tile is
-// quantised now, so whole words are written without checks; otherwise only
-// the codes of positions with quant(p) are merged into what the page holds.
-template <int D, int BITS, typename Pred>
-__device__ void value_words(uint16_t *vt, int32_t blk_lo, Pred quant, bool full, uint8_t *pg, int tid)
+// Phase C of a tile: the value-code words of its tokens [t0, t1) (both
+// multiples of 8: a word holds eight tokens), from the code bytes that phase
+// B left in the value rows (vcode_row).
+//
+// Four channels a thread: it reads their code bytes of a token as one word,
+// gathers the tokens whose codes share byte k of the output words into word k
+// (the codes leave the upper bits of their bytes free, and no field of a word
+// crosses a byte), and transposes the four words' bytes: 16 reads and 20
+// vector instructions for four 2-bit words, where a byte read and a shift-or
+// per code took 64.
+template <int D, int BITS>
+__device__ void whole_value_words(uint16_t *vt, int t0, int t1, uint8_t *pg, int tid)
 {
     using L = Layout<D, BITS>;
-    constexpr int kPitch = D + 8;
-    if (full) {
-        // Four channels a thread: it reads their code bytes of a token as
-        // one word, gathers the tokens whose codes share byte k of the
-        // output words into word k (the codes leave the upper bits of their
-        // bytes free, and no field of a word crosses a byte), and transposes
-        // the four words' bytes: 16 reads and 20 vector instructions for
-        // four 2-bit words, where a byte read and a shift-or per code took 64.
-        uint32_t *vreg = reinterpret_cast<uint32_t *>(pg + L::kRegionBytes);
-        constexpr int kU = 2 * L::kNw;       // words of a lane and 32-token slice
-        constexpr int kItems = 2 * kU * 16;  // (32-token slice, j, four channels, u)
-        constexpr int kRowBytes = 2 * kPitch;
-        for (int idx = tid; idx < kItems; idx += 256) {
-            const int u = idx % kU, m0 = 4 * ((idx / kU) & 3), j = (idx / (4 * kU)) & 3, kc = idx / (16 * kU);
-            const uint8_t *base = vcode_row<D>(vt, 32 * kc + 8 * j);  // token i at + i kRowBytes
-            uint32_t g[4] = {0u, 0u, 0u, 0u};
+    constexpr int kRowBytes = 2 * (D + 8);
+    uint32_t *vreg = reinterpret_cast<uint32_t *>(pg + L::kRegionBytes);
+    constexpr int kU = 2 * L::kNw;  // words of a lane and 32-token slice
+    // items: (eight tokens, four channels, u)
+    for (int idx = (t0 / 8) * 4 * kU + tid; idx < (t1 / 8) * 4 * kU; idx += 256) {
+        const int u = idx % kU, m0 = 4 * ((idx / kU) & 3), j = (idx / (4 * kU)) & 3, kc = idx / (16 * kU);
+        const uint8_t *base = vcode_row<D>(vt, 32 * kc + 8 * j);  // token i at + i kRowBytes
+        uint32_t g[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-            for (int e = 0; e < L::kCodesPerWord; ++e) {
-                const int o = e >> 3, i = e & 7;
-                const int ch = 16 * (u * L::kOpsPerWord + o) + m0;
-                const uint32_t codes =
-                    *reinterpret_cast<const uint32_t *>(base + i * kRowBytes + ch + (ch >= D / 2 ? D / 2 : 0));
-                g[L::v_bit(o, i) / 8] |= codes << (L::v_bit(o, i) % 8);
-            }
-            // bytes (0, 1) and (2, 3) of each pair of words interleaved, then
-            // the halves joined: word c is byte c of g[0 .. 3]
-            const uint32_t a0 = __builtin_amdgcn_perm(g[1], g[0], 0x05010400u);
-            const uint32_t a1 = __builtin_amdgcn_perm(g[1], g[0], 0x07030602u);
-            const uint32_t b0 = __builtin_amdgcn_perm(g[3], g[2], 0x05010400u);
-            const uint32_t b1 = __builtin_amdgcn_perm(g[3], g[2], 0x07030602u);
-            const uint32_t word[4] = {
-                __builtin_amdgcn_perm(b0, a0, 0x05040100u), __builtin_amdgcn_perm(b0, a0, 0x07060302u),
-                __builtin_amdgcn_perm(b1, a1, 0x05040100u), __builtin_amdgcn_perm(b1, a1, 0x07060302u)};
-#pragma unroll
-            for (int c = 0; c < 4; ++c) vreg[L::v_word(16 * j + m0 + c, kc * kU + u)] = word[c];
+        for (int e = 0; e < L::kCodesPerWord; ++e) {
+            const int o = e >> 3, i = e & 7;
+            const int ch = 16 * (u * L::kOpsPerWord + o) + m0;
+            const uint32_t codes =
+                *reinterpret_cast<const uint32_t *>(base + i * kRowBytes + ch + (ch >= D / 2 ? D / 2 : 0));
+            g[L::v_bit(o, i) / 8] |= codes << (L::v_bit(o, i) % 8);
         }
-    } else if (pg != nullptr) {
+        // bytes (0, 1) and (2, 3) of each pair of words interleaved, then
+        // the halves joined: word c is byte c of g[0 .. 3]
+        const uint32_t a0 = __builtin_amdgcn_perm(g[1], g[0], 0x05010400u);
+        const uint32_t a1 = __builtin_amdgcn_perm(g[1], g[0], 0x07030602u);
+        const uint32_t b0 = __builtin_amdgcn_perm(g[3], g[2], 0x05010400u);
+        const uint32_t b1 = __builtin_amdgcn_perm(g[3], g[2], 0x07030602u);
+        const uint32_t word[4] = {
+            __builtin_amdgcn_perm(b0, a0, 0x05040100u), __builtin_amdgcn_perm(b0, a0, 0x07060302u),
+            __builtin_amdgcn_perm(b1, a1, 0x05040100u), __builtin_amdgcn_perm(b1, a1, 0x07060302u)};
+#pragma unroll
+        for (int c = 0; c < 4; ++c) vreg[L::v_word(16 * j + m0 + c, kc * kU + u)] = word[c];
+    }
+}
+
+// Phase C for any set of positions of the tile: the codes of positions with
+// quant(p) merged into what the page holds.
+template <int D, int BITS, typename Pred>
+__device__ void value_words(uint16_t *vt, int32_t blk_lo, Pred quant, uint8_t *pg, int tid)
+{
+    using L = Layout<D, BITS>;
+    if (pg != nullptr) {
         uint32_t *vreg = reinterpret_cast<uint32_t *>(pg + L::kRegionBytes);
         constexpr int kWords = 64 * L::kWordsPerLane;
         for (int idx = tid; idx < kWords; idx += 256) {
@@ -617,7 +623,8 @@ __device__ void quantise_tile(const AppendArgs &a, const uint16_t *kt, uint16_t 
     }
     __syncthreads();
 
-    value_words<D, BITS>(vt, blk_lo, quant, full, pg, tid);
+    if (full) whole_value_words<D, BITS>(vt, 0, kPage, pg, tid);
+    else value_words<D, BITS>(vt, blk_lo, quant, pg, tid);
 }
 
 // ------------------------------------------------ few positions, wide groups
@@ -728,15 +735,15 @@ __device__ __forceinline__ void few_order_stats_of(int K, const uint32_t (&w)[kR
     else if constexpr (KC < 16) few_order_stats_of<kRegs, KC + 1>(K, w, a_lo, a_hi, mn, mx);
 }
 
-// Phases B and C for at most 8 positions [lo, hi) of the tile at blk_lo (one
-// page, pg, or null outside the pool), with 16 lanes per quantisation group:
-// group g = tid / 16 is the key row (g < 8) or the value row (g >= 8) of
-// position lo + g % 8, lane s = tid % 16 holds its channels kPer s ..
-// kPer s + kPer - 1.  The parameters, codes and words are those
-// quantise_tile writes (the selection keeps the same multiset; the QuEST sum
-// of squares is exact in fp64 for bf16 inputs of the usual range, so its
-// order does not matter).  Needs D - lo_k and D - lo_v <= 16 for Eq. (7).
-// Every thread of the workgroup calls it.
+// Phases B and C for a short range of positions [lo, hi) of the tile at
+// blk_lo (one page, pg, or null outside the pool), eight at a time with 16
+// lanes per quantisation group: group g = tid / 16 is the key row (g < 8) or
+// the value row (g >= 8) of position lo + g % 8 (then lo + 8 + g % 8, ..),
+// lane s = tid % 16 holds its channels kPer s .. kPer s + kPer - 1.  The
+// parameters, codes and words are those quantise_tile writes (the selection
+// keeps the same multiset; the QuEST sum of squares is exact in fp64 for bf16
+// inputs of the usual range, so its order does not matter).  Needs D - lo_k
+// and D - lo_v <= 16 for Eq. (7).  Every thread of the workgroup calls it.
 template <int D, int BITS>
 __device__ void quantise_few(const AppendArgs &a, uint16_t *kt, uint16_t *vt, int32_t blk_lo,
                              int32_t lo, int32_t hi, uint8_t *pg, int tid)
@@ -750,8 +757,8 @@ __device__ void quantise_few(const AppendArgs &a, uint16_t *kt, uint16_t *vt, in
     constexpr int kLanesPerWord = kPerWord / kPer;  // 1, 2 or 4
     const int g = tid >> 4, sl = tid & 15;
     const bool is_v = g >= 8;
-    const int r = (lo - blk_lo) + (g & 7);
-    if ((g & 7) < hi - lo && pg != nullptr) {  // uniform over the group's 16 lanes
+    const int r0 = lo - blk_lo, r1 = hi - blk_lo;
+    for (int r = r0 + (g & 7); r < r1 && pg != nullptr; r += 8) {  // uniform over the group's 16 lanes
         uint16_t *row = (is_v ? vt : kt) + r * kPitch;
         const int ch0 = kPer * sl;
         uint32_t w[kPer / 2];
@@ -830,21 +837,22 @@ __device__ void quantise_few(const AppendArgs &a, uint16_t *kt, uint16_t *vt, in
         }
     }
     __syncthreads();
-    value_words<D, BITS>(vt, blk_lo, [&](int32_t p) { return p >= lo && p < hi; }, false, pg, tid);
+    if (pg != nullptr && ((r0 | r1) & 7) == 0) whole_value_words<D, BITS>(vt, r0, r1, pg, tid);
+    else value_words<D, BITS>(vt, blk_lo, [&](int32_t p) { return p >= lo && p < hi; }, pg, tid);
 }
 
 // Quantise positions [start, q_new) of (sequence b, kv head h) into their
 // pages, one 64-position block at a time (Alg. 2 steps 7-11).  A position
 // before s_ring comes from the windows' ring (keys row-major, values
 // channel-major); one at or after it is a new token of this call, its key
-// already transformed in kn (LDS, pitch D + 8) and its value in v_new.  kt
-// and vt are 64-row LDS tiles, sh one LDS word.  Every thread of the
-// 256-thread workgroup calls it.  kNewRows false: every position comes from
-// the ring (s_ring and kn unused).
+// already transformed in kn and its value in vn (LDS, pitch D + 8).  kt and
+// vt are 64-row LDS tiles, sh one LDS word.  Every thread of the 256-thread
+// workgroup calls it.  kNewRows false: every position comes from the ring
+// (s_ring, kn and vn unused).
 template <int D, int BITS, bool kNewRows>
 __device__ void flush_range(const AppendArgs &a, int b, int h, int32_t start, int32_t q_new,
-                            int32_t s_ring, const uint16_t *kn, uint16_t *kt, uint16_t *vt,
-                            int32_t *sh, int tid)
+                            int32_t s_ring, const uint16_t *kn, const uint16_t *vn, uint16_t *kt,
+                            uint16_t *vt, int32_t *sh, int tid)
 {
     using L = Layout<D, BITS>;
     constexpr int kPitch = D + 8;
@@ -853,15 +861,14 @@ __device__ void flush_range(const AppendArgs &a, int b, int h, int32_t start, in
     const int64_t head_win = ((int64_t)b * a.n_kv + h) * a.win_slots;
     for (int32_t blk = a.s_sink + (start - a.s_sink) / kPage * kPage; blk < q_new; blk += kPage) {
         const int32_t lo = max(blk, start), hi = min(blk + kPage, q_new);
-        for (int idx = tid; idx < kPage * kVec; idx += 256) {
-            const int r = idx / kVec, cv = idx % kVec;
-            const int32_t p = blk + r;
-            if (p < lo || p >= hi) continue;
+        for (int idx = tid; idx < (hi - lo) * kVec; idx += 256) {
+            const int cv = idx % kVec;
+            const int32_t p = lo + idx / kVec;
+            const int r = p - blk;
             uint4 kv, vv;
             if (kNewRows && p >= s_ring) {
                 kv = *reinterpret_cast<const uint4 *>(kn + (p - s_ring) * kPitch + 8 * cv);
-                vv = *reinterpret_cast<const uint4 *>(
-                    a.v_new + (((int64_t)b * a.max_new + (p - s_ring)) * a.n_kv + h) * D + 8 * cv);
+                vv = *reinterpret_cast<const uint4 *>(vn + (p - s_ring) * kPitch + 8 * cv);
             } else {
                 const int32_t slot = ring_slot(p, a.s_sink, ring);
                 kv = *reinterpret_cast<const uint4 *>(a.win_k + (head_win + slot) * D + 8 * cv);
@@ -889,8 +896,10 @@ __device__ void flush_range(const AppendArgs &a, int b, int h, int32_t start, in
         __syncthreads();
         const int32_t page = sh[0];
         uint8_t *pg = page >= 0 ? a.pages + ((int64_t)page * a.n_kv + h) * L::kPageBytes : nullptr;
-        // a short range (a decode step's flush): 16 lanes per group
-        const bool few = hi - lo <= 8 &&
+        // a short range (the flush of a decode step or of a 16-token chunk):
+        // 16 lanes per group (of 16 rows the lane-pair tile would keep a
+        // quarter of its lanes busy, for as long as all 64 take)
+        const bool few = hi - lo <= 16 &&
                          (a.codec == WUSHKV_CODEC_QUEST || (D - a.lo_k <= 16 && D - a.lo_v <= 16));
         if (few)
             quantise_few<D, BITS>(a, kt, vt, blk, lo, hi, pg, tid);
