@@ -474,7 +474,8 @@ static hipError_t launch_append_step(const AppendArgs &a, dim3 grid, hipStream_t
 struct FinishArgs {
     const float *part;  // [batch][n_kv][n_splits][G][D + 2]
     float *out;         // [batch][n_kv G][D]
-    int32_t G, n_splits;
+    int32_t G, n_splits, n_page_splits;
+    const int32_t *runs;  // the attention launch's page runs (MergeRows)
     int32_t merge_wgs;  // workgroups that merge, per sequence: n_q, or a quarter
     bool merge_one;     // a wave to a row (merge_by_one)
 };
@@ -494,11 +495,10 @@ __global__ void __launch_bounds__(256) step_finish_kernel(AppendArgs a, FinishAr
         const int qh = f.merge_one ? 4 * (int)blockIdx.x + (tid >> 6) : (int)blockIdx.x;
         if (qh >= n_q) return;
         const int h = qh / f.G, g = qh % f.G;
-        const int64_t stride = (int64_t)f.G * (D + 2);
-        const float *pp = f.part + ((int64_t)b * a.n_kv + h) * f.n_splits * stride + g * (D + 2);
+        const MergeRows rows{f.part, a.n_kv, f.G, f.n_splits, f.n_page_splits, b, h, g, f.runs};
         float *dst = f.out + ((int64_t)b * n_q + qh) * D;
-        if (f.merge_one) merge_splits<D, 1>(pp, stride, f.n_splits, dst, tid, merge);
-        else merge_splits<D, 4>(pp, stride, f.n_splits, dst, tid, merge);
+        if (f.merge_one) merge_splits<D, 1>(rows, dst, tid, merge);
+        else merge_splits<D, kMergeWaves>(rows, dst, tid, merge);
         return;
     }
     const int h = (int)blockIdx.x - f.merge_wgs;
@@ -683,7 +683,8 @@ extern "C" int wushkv_append_norm_rope(const wushkv_cache *c, const uint16_t *k_
 // The finishing launch of wushkv_decode_step (its attention launch precedes
 // it on the stream): see step_finish_kernel.  Declared in decode.hip.
 int wushkv_step_finish(const wushkv_cache *c, const int32_t *n_new, const float *part, float *out,
-                       int32_t G, int32_t n_splits, hipStream_t s)
+                       int32_t G, int32_t n_splits, int32_t n_page_splits, const int32_t *runs,
+                       hipStream_t s)
 {
     AppendArgs a = cache_args(c);
     a.n_new = n_new;
@@ -691,7 +692,7 @@ int wushkv_step_finish(const wushkv_cache *c, const int32_t *n_new, const float 
     a.arrivals = c->n_kv_heads;  // the flush workgroups of a sequence
     const int32_t n_q = c->n_kv_heads * G;
     const bool one = merge_by_one((int64_t)n_q * c->batch);
-    FinishArgs f{part, out, G, n_splits, one ? (n_q + 3) / 4 : n_q, one};
+    FinishArgs f{part, out, G, n_splits, n_page_splits, runs, one ? (n_q + 3) / 4 : n_q, one};
     const dim3 grid((unsigned)(f.merge_wgs + c->n_kv_heads), (unsigned)c->batch);
     const int key = c->head_dim * 10 + storage_bits(c->bits);
     switch (key) {

@@ -112,6 +112,11 @@ struct DecodeArgs {
     const uint16_t *v_new;  // bf16 [batch][n_kv][D]
     const uint16_t *t_k;    // bf16 [n_kv][D][D]
     uint16_t *win_kw, *win_vw;  // the windows, written
+    // the page runs as dealt out, for the merge (null: every row has its own
+    // n_page_splits splits); even: each sequence's pages are at least shared
+    // evenly by its own workgroups; see plan_runs
+    int32_t *runs;
+    bool even;
 };
 
 // Tokens of sequence b's chunk: n_tok[b] (or max_tok), at most max_tok and
@@ -692,6 +697,79 @@ __device__ void step_token(const DecodeArgs &a, int b, int h, int32_t slot, uint
     __syncthreads();
 }
 
+// The page run of a workgroup, by the lengths the launch finds.  The grid is
+// sized for max_seq_len: n_page_splits page workgroups per sequence, numbered
+// b n_page_splits + split through the batch.  A sequence's own workgroups share
+// its pages evenly, in runs of u_own = ceil(pages / (4 n_page_splits)) per
+// wave.  If the lengths are ragged the longest one's runs then set the launch's
+// time while other workgroups have little or nothing to do, so where runs of
+// fewer pages than its u_own can be had by dealing all the workgroups out in
+// proportion to the pages (sequence l takes ceil(pages_l / (4 u)) consecutive
+// ones, with the least u for which they suffice), they are: eight sequences of
+// 1500 to 12000 tokens, eight heads, 4-bit, take 35.0 us a call instead of 38.2.  Every wave of the launch
+// works this out for itself from the counters (lane l, sequence l: batches of
+// at most 64); the first workgroup notes it for the merge.
+struct PageRun {
+    int32_t b, hi, n_pages;  // the sequence, the end of its quantised positions, its pages
+    int32_t first, u;        // the workgroup's first page, pages per wave
+    bool idle;
+};
+// One sequence's own workgroups share its pages.
+__device__ __forceinline__ PageRun own_run(const DecodeArgs &a, int b, int split, int32_t hi, int32_t n_pages)
+{
+    const int32_t P = a.n_page_splits;
+    const int32_t u = min(max((n_pages + 4 * P - 1) / (4 * P), 1), 64);
+    return PageRun{b, hi, n_pages, 4 * split * u, u, false};
+}
+struct RunCounters {
+    int32_t s, q, nn;  // of sequence `lane` (zeros beyond the batch)
+    __device__ __forceinline__ void load(const DecodeArgs &a, int lane)
+    {
+        s = q = nn = 0;
+        if (lane < (int)gridDim.z) {
+            s = a.seq_len[lane];
+            q = a.quant_end[lane];
+            if (a.n_new != nullptr) nn = a.n_new[lane];
+        }
+    }
+};
+__device__ __forceinline__ PageRun plan_runs(const DecodeArgs &a, const RunCounters &c, int b, int split, int h,
+                                             int wave, int lane)
+{
+    const int32_t B = gridDim.z, P = a.n_page_splits;
+    const int32_t S = c.s + (c.nn < 0 ? 0 : (c.nn > 1 ? 1 : c.nn));
+    const int32_t hi = max(min(c.q, S), a.s_sink);
+    const int32_t pages = (hi - a.s_sink + kPage - 1) / kPage;
+    // (page counts are exact in fp32: at most 2^24 in all)
+    const int32_t most = __builtin_amdgcn_readfirstlane((int32_t)wave_max((float)pages));
+    const int32_t all = __builtin_amdgcn_readfirstlane((int32_t)wave_sum((float)pages));
+    const int32_t u_own = max((most + 4 * P - 1) / (4 * P), 1);
+    int32_t u = max((all + 4 * P * B - 1) / (4 * P * B), 1), wgs = 0;
+    for (; u < u_own; ++u) {
+        wgs = (pages + 4 * u - 1) / (4 * u);
+        if (__builtin_amdgcn_readfirstlane((int32_t)wave_sum((float)wgs)) <= P * B) break;
+    }
+    const bool note = h == 0 && b == 0 && split == 0 && wave == 0;
+    if (u >= u_own) {
+        if (note && lane == 0) a.runs[0] = 0;
+        return own_run(a, b, split, __builtin_amdgcn_readlane(hi, b), __builtin_amdgcn_readlane(pages, b));
+    }
+    const int32_t end = wave_scan(wgs), start = end - wgs;
+    if (note) {
+        if (lane == 0) a.runs[0] = 1;
+        if (lane < B) {
+            a.runs[2 + 2 * lane] = start;
+            a.runs[2 + 2 * lane + 1] = wgs;
+        }
+    }
+    const int32_t i = b * P + split;
+    const uint64_t mine = __ballot(lane < B && start <= i && i < end);
+    if (mine == 0) return PageRun{b, a.s_sink, 0, 0, 1, true};
+    const int l = __builtin_ctzll(mine);
+    return PageRun{l, __builtin_amdgcn_readlane(hi, l), __builtin_amdgcn_readlane(pages, l),
+                   4 * u * (i - __builtin_amdgcn_readlane(start, l)), u, false};
+}
+
 // FORM: the workgroup forms q~ and its limbs itself (the grid fits on the
 // device at once); otherwise decode_qt_kernel has written them.
 // SHARE (chunks, with decode_qt_kernel): the four waves of a workgroup take
@@ -743,10 +821,15 @@ decode_main_kernel(DecodeArgs a)
     // of q~, and the page-table entries of this wave's run (a run's share
     // beyond the sequence's pages is not used)
     const bool page_wg = split < a.n_page_splits;
-    const int upw = a.units_per_wave;
-    const int w0 = page_wg ? (SHARE ? split : split * 4 + wave) * upw : 0;
+    int upw = a.units_per_wave;
+    int w0 = page_wg ? (SHARE ? split : split * 4 + wave) * upw : 0;
+    // (the counters of plan_runs before those: loads complete in order)
     QueryIn<D, G> qin;
-    if constexpr (FORM) qin.load_t(a, h, tid);
+    RunCounters counters;
+    if constexpr (FORM) {
+        if (page_wg && a.runs != nullptr) counters.load(a, lane);
+        qin.load_t(a, h, tid);
+    }
     int32_t tbl = -1;
     if (page_wg && a.n_pages > 0 && lane < upw && w0 + lane < a.max_pages)
         tbl = a.page_table[(int64_t)b * a.max_pages + w0 + lane];
@@ -764,8 +847,26 @@ decode_main_kernel(DecodeArgs a)
     // per-wave results for the merge: o (unnormalised, relative to m), m, l
     float(*sC)[D] = reinterpret_cast<float(*)[D]>(stage);
 
-    const int w1 = page_wg && rows_live ? min(w0 + upw, n_qpages) : 0;
-    if constexpr (FORM) qin.load_q(a, b, tg, h, S, tid);
+    int w1 = page_wg && rows_live ? min(w0 + upw, n_qpages) : 0;
+    int32_t p_hi = q_hi;  // the end of the quantised positions of the run's sequence
+    if constexpr (FORM) {
+        qin.load_q(a, b, tg, h, S, tid);
+        if (page_wg && a.even) {
+            const PageRun pr = a.runs != nullptr ? plan_runs(a, counters, b, split, h, wave, lane)
+                                                 : own_run(a, b, split, q_hi, n_qpages);
+            if (pr.idle) return;
+            p_hi = pr.hi;
+            w0 = pr.first + wave * pr.u;
+            w1 = min(w0 + pr.u, pr.n_pages);
+            if (pr.b != b || pr.u != upw) {  // not what was requested above
+                upw = pr.u;
+                tbl = -1;
+                if (a.n_pages > 0 && lane < upw && w0 + lane < a.max_pages)
+                    tbl = a.page_table[(int64_t)pr.b * a.max_pages + w0 + lane];
+            }
+            if (pr.b != b) qin.load_q(a, pr.b, tg, h, S, tid);
+        }
+    }
     using Q = QueryLds<D, G>;
     uint8_t *qrows = lds + M::kRowsAt;
     const int64_t row0 = ((int64_t)bz * a.n_kv + h) * G;  // first (virtual) query head
@@ -922,7 +1023,7 @@ decode_main_kernel(DecodeArgs a)
                 const int32_t phys = phys_of(u);
                 // a page outside the pool contributes nothing (its stage holds page 0)
                 const int32_t nvalid = (phys < 0 || phys >= a.n_pages)
-                                           ? 0 : min(kPage, q_hi - (a.s_sink + u * kPage));
+                                           ? 0 : min(kPage, p_hi - (a.s_sink + u * kPage));
                 const u32x4 kp = kx[kKX], vp = kx[kKX + 1];
 
                 // scores: one product per 16 tokens, head group and limb group;
@@ -2081,9 +2182,8 @@ __global__ void __launch_bounds__(64 * NW) decode_combine_kernel(const float *pa
             return;
         }
     }
-    const int64_t stride = (int64_t)G * (D + 2);
-    const float *pp = part + (((int64_t)bz * n_kv + h) * n_splits) * stride + g * (D + 2);
-    merge_splits<D, NW>(pp, stride, n_splits, dst, tid, lds);
+    const MergeRows rows{part, n_kv, G, n_splits, a.n_page_splits, bz, h, g, a.runs};
+    merge_splits<D, NW>(rows, dst, tid, lds);
 }
 
 // ------------------------------------------------------------------ host
@@ -2336,7 +2436,8 @@ struct StepIn {
 };
 
 int wushkv_step_finish(const wushkv_cache *c, const int32_t *n_new, const float *part, float *out,
-                       int32_t G, int32_t n_splits, hipStream_t s);  // append.hip
+                       int32_t G, int32_t n_splits, int32_t n_page_splits, const int32_t *runs,
+                       hipStream_t s);  // append.hip
 
 static int attend(const wushkv_cache *c, const uint16_t *q, const int32_t *n_tok, int32_t max_tok,
                   int32_t n_q_heads, int32_t max_seq_len, const float *t_k_inv, float sm_scale,
@@ -2414,6 +2515,12 @@ static int attend(const wushkv_cache *c, const uint16_t *q, const int32_t *n_tok
     const int64_t wgs = (int64_t)p.n_splits * c->n_kv_heads * grid_z;
     const bool form = !rs.share && p.win_units == 1 &&
                       wgs * 4 <= resident_waves(c->head_dim, storage_bits(c->bits), G, false);
+    // such a grid also deals its page runs out by the lengths it finds (one
+    // lane per sequence), noted where the query rows' aux words would be
+    a.even = form && max_tok == 1 && n_tok == nullptr && p.n_page_splits > 0;
+    if (a.even && c->batch > 1 && c->batch <= 64 &&
+        p.aux_bytes >= (2 + 2 * (size_t)c->batch) * sizeof(int32_t))
+        a.runs = reinterpret_cast<int32_t *>(qaux);
     const int key = c->head_dim * 10 + storage_bits(c->bits);
     if (rs.share && c->head_dim == 128 && G == 8) {
         // chunks: q~ rows (chunk_qt_kernel), the pages (chunk_pages_kernel, splits 0 ..
@@ -2441,7 +2548,7 @@ static int attend(const wushkv_cache *c, const uint16_t *q, const int32_t *n_tok
     }
     if (step != nullptr) {
         if (hipGetLastError() != hipSuccess) return WUSHKV_ELAUNCH;
-        return wushkv_step_finish(c, step->n_new, part, out, G, p.n_splits, s);
+        return wushkv_step_finish(c, step->n_new, part, out, G, p.n_splits, p.n_page_splits, a.runs, s);
     }
     auto combine = [&](auto kernel, int nw) {
         launch("decode_combine_kernel", kernel, gc, dim3(64 * nw), s, (const float *)part, out, c->n_kv_heads, G,

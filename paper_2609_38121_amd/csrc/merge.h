@@ -16,6 +16,22 @@ __device__ __forceinline__ float dpp(float x)
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, false));
 }
+// Inclusive prefix sum over the lanes.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int32_t dpp_from(int32_t x)  // 0 where there is no such lane
+{
+    return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ int32_t wave_scan(int32_t x)
+{
+    x += dpp_from<0x111, 0xF>(x);  // row_shr 1, 2, 4, 8
+    x += dpp_from<0x112, 0xF>(x);
+    x += dpp_from<0x114, 0xF>(x);
+    x += dpp_from<0x118, 0xF>(x);
+    x += dpp_from<0x142, 0xA>(x);  // lane 15 of a row to the next row
+    x += dpp_from<0x143, 0xC>(x);  // lane 31 to the upper half
+    return x;
+}
 // x of this lane and of lane ^ 16, ^ 32 (which comes first varies).
 struct LanePair {
     float a, b;
@@ -84,8 +100,22 @@ struct MergeLds {
     float m[kMergeWaves], l[kMergeWaves];
 };
 
-// One query head: the n_splits partials (o[D] relative to m, m, l) at pp,
-// pp + stride, ..  (m in base 2) merge into
+// Where a row's partials are: query head (h, g) of grid row b, among part's
+// [grid row][n_kv][n_splits][G][D + 2].  The window partials are the row's own
+// splits from n_page_splits on; so are the page partials, at the splits before,
+// unless the attention launch dealt its page runs out by the lengths it found
+// (runs, see plan_runs in decode.hip): runs[0] is then not zero and the row's
+// page partials are those of the runs[2 + 2 b + 1] page workgroups from number
+// runs[2 + 2 b] on, numbered through all the rows.
+struct MergeRows {
+    const float *part;
+    int32_t n_kv, G, n_splits, n_page_splits;
+    int32_t b, h, g;
+    const int32_t *runs;
+};
+
+// One query head: its n partials (o[D] relative to m, m, l; m in base 2) merge
+// into
 //   dst = sum_s 2^(m_s - M) o_s / sum_s 2^(m_s - M) l_s,  M = max_s m_s,
 // zero when no split saw a position.  NW waves share the splits (wave w takes
 // w, w + NW, ..): lane i loads m and l of the wave's i-th split, the wave
@@ -93,42 +123,65 @@ struct MergeLds {
 // together with them, are added up with each weight read from its lane.  The
 // merge is a latency chain: one round trip to memory instead of two, and one
 // barrier (none for one wave) instead of nine (89 splits: 4.6 instead of 7.4
-// us, near a launch's own cost).  With NW = 1 each wave merges
-// a row of its own.
+// us, near a launch's own cost).  The row's own splits are requested before
+// runs[0] is known, and again where the runs were dealt out.  With NW = 1 each
+// wave merges a row of its own.
 template <int D, int NW>
-__device__ __forceinline__ void merge_splits(const float *pp, int64_t stride, int32_t n_splits,
-                                             float *dst, int tid, MergeLds<D> &lds)
+__device__ __forceinline__ void merge_splits(const MergeRows &r, float *dst, int tid, MergeLds<D> &lds)
 {
     constexpr int kPer = D / 64;     // channels per lane
     constexpr int kFirst = 8;        // rows of o requested at once, and, where
     constexpr int kMore = 16;        // there are more, with them
     const int lane = tid & 63, wave = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int32_t mine = (n_splits - wave + NW - 1) / NW;  // this wave's splits
-    const float *base = pp + wave * stride;
-    const int64_t step = NW * stride;
-    float M = -INFINITY, l = 0.0f, o[kPer];
+    const int64_t stride = (int64_t)r.G * (D + 2);
+    const float *base = r.part + r.g * (D + 2);
+    const int32_t own = (r.b * r.n_kv + r.h) * r.n_splits;
+    int32_t total = r.n_splits;      // the row's partials
+    int32_t first = 0, n_runs = -1;  // dealt out: its page runs
+    int32_t slot = own;              // partial of the wave's (k0 + lane)-th split
+    int32_t n = 0;                   // the wave's splits of this pass, at most 64
+    float ms, ls, x[kFirst][kPer], y[kMore][kPer];
+    // (a row past the end is a repeat of the last)
+    auto load_rows = [&](auto &v, int32_t i0) {
 #pragma unroll
-    for (int e = 0; e < kPer; ++e) o[e] = 0.0f;
-    for (int32_t k0 = 0; k0 < mine; k0 += 64) {
-        const int32_t n = min(mine - k0, 64);
-        float ms = -INFINITY, ls = 0.0f;
+        for (int i = 0; i < (int)(sizeof(v) / sizeof(v[0])); ++i) {
+            const int32_t sl = __builtin_amdgcn_readlane(slot, min(i0 + i, n - 1));
+            const float *src = base + (int64_t)sl * stride + kPer * lane;
+#pragma unroll
+            for (int e = 0; e < kPer; ++e) v[i][e] = src[e];
+        }
+    };
+    auto fetch = [&](int32_t k0) {
+        n = min((total - wave + NW - 1) / NW - k0, 64);
+        const int32_t s = min(wave + NW * (k0 + lane), total - 1);
+        slot = own + s;
+        if (n_runs >= 0) {
+            const int32_t i = first + s;
+            slot = s < n_runs ? ((i / r.n_page_splits) * r.n_kv + r.h) * r.n_splits + i % r.n_page_splits
+                              : own + r.n_page_splits + (s - n_runs);
+        }
+        ms = -INFINITY;
+        ls = 0.0f;
+        if (n <= 0) return;
         if (lane < n) {
-            const float *src = base + (k0 + lane) * step + D;
+            const float *src = base + (int64_t)slot * stride + D;
             ms = src[0];
             ls = src[1];
         }
-        // (a row past the end is a repeat of the last)
-        auto load_rows = [&](auto &x, int32_t i0) {
-#pragma unroll
-            for (int i = 0; i < (int)(sizeof(x) / sizeof(x[0])); ++i) {
-                const float *src = base + (int64_t)(k0 + min(i0 + i, n - 1)) * step + kPer * lane;
-#pragma unroll
-                for (int e = 0; e < kPer; ++e) x[i][e] = src[e];
-            }
-        };
-        float x[kFirst][kPer], y[kMore][kPer];
         load_rows(x, 0);
         if (n > kFirst) load_rows(y, kFirst);
+    };
+    fetch(0);
+    if (r.runs != nullptr && r.runs[0] != 0) {
+        first = r.runs[2 + 2 * r.b];
+        n_runs = r.runs[2 + 2 * r.b + 1];
+        total = n_runs + r.n_splits - r.n_page_splits;
+        fetch(0);
+    }
+    float M = -INFINITY, l = 0.0f, o[kPer];
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) o[e] = 0.0f;
+    for (int32_t k0 = 0; n > 0;) {
         const float m_new = fmaxf(M, wave_max(ms));
         const float f = M == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(M - m_new);
         const float w = ms == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(ms - m_new);
@@ -136,13 +189,13 @@ __device__ __forceinline__ void merge_splits(const float *pp, int64_t stride, in
 #pragma unroll
         for (int e = 0; e < kPer; ++e) o[e] *= f;
         M = m_new;
-        auto add_rows = [&](const auto &x, int32_t i0) {
+        auto add_rows = [&](const auto &v, int32_t i0) {
 #pragma unroll
-            for (int i = 0; i < (int)(sizeof(x) / sizeof(x[0])); ++i) {
+            for (int i = 0; i < (int)(sizeof(v) / sizeof(v[0])); ++i) {
                 // (lane i0 + i holds weight 0 past the end)
                 const float wi = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w), i0 + i));
 #pragma unroll
-                for (int e = 0; e < kPer; ++e) o[e] = fmaf(wi, x[i][e], o[e]);
+                for (int e = 0; e < kPer; ++e) o[e] = fmaf(wi, v[i][e], o[e]);
             }
         };
         add_rows(x, 0);
@@ -150,6 +203,8 @@ __device__ __forceinline__ void merge_splits(const float *pp, int64_t stride, in
             if (i0 > kFirst) load_rows(y, i0);
             add_rows(y, i0);
         }
+        k0 += 64;
+        fetch(k0);
     }
     if constexpr (NW == 1) {
 #pragma unroll
