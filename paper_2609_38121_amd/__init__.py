@@ -14,6 +14,7 @@ from __future__ import annotations
 
 import ctypes
 import math
+import operator
 
 from . import _lib
 from ._lib import (CacheDesc, WushKVError, PAGE_TOKENS, check, header_functions,
@@ -40,9 +41,15 @@ def _ptr(t) -> int | None:
 
 
 def _stream_handle(stream) -> int:
+    if stream is not None:
+        return stream.cuda_stream
     torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream
+    # the current stream's handle without a Stream object (2.8 us a call, as
+    # much as a kernel launch)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 def wushkv_page_bytes(head_dim: int, bits: int) -> int:
@@ -215,6 +222,23 @@ def wushkv_append_norm_rope(cache: WushKVCache, k_raw, v_new, n_new, t_k, rope_t
     check(st, "wushkv_append_norm_rope")
 
 
+def _decode_need(cache, n_q, max_seq_len) -> int:
+    """The workspace size, or the error for sizes that have no plan (only
+    asked for where no workspace is given, or after a call was refused: the
+    library checks a given workspace itself)."""
+    need = wushkv_decode_workspace_bytes(cache, n_q, max_seq_len)
+    if need == 0:
+        raise WushKVError(_lib.EINVAL, "wushkv_decode_workspace_bytes")
+    return need
+
+
+def _chunk_need(cache, n_q, max_tok, max_seq_len) -> int:
+    need = wushkv_chunk_workspace_bytes(cache, n_q, max_tok, max_seq_len)
+    if need == 0:
+        raise WushKVError(_lib.EINVAL, "wushkv_chunk_workspace_bytes")
+    return need
+
+
 def wushkv_decode_workspace_bytes(cache: WushKVCache, n_q_heads: int, max_seq_len: int) -> int:
     return _lib.lib().wushkv_decode_workspace_bytes(ctypes.byref(cache.desc), n_q_heads,
                                                     max_seq_len)
@@ -233,16 +257,15 @@ def wushkv_decode_attention(cache: WushKVCache, q, t_k_inv, sm_scale=None, max_s
         sm_scale = 1.0 / math.sqrt(cache.head_dim)
     if out is None:
         out = torch.empty(cache.batch, n_q, cache.head_dim, dtype=torch.float32, device=q.device)
-    need = wushkv_decode_workspace_bytes(cache, n_q, max_seq_len)
-    if need == 0:
-        raise WushKVError(_lib.EINVAL, "wushkv_decode_workspace_bytes")
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+        workspace = torch.empty(_decode_need(cache, n_q, max_seq_len), dtype=torch.uint8, device=q.device)
     st = _lib.lib().wushkv_decode_attention(
-        ctypes.byref(cache.desc), _ptr(q), n_q, int(max_seq_len), _ptr(t_k_inv),
+        ctypes.byref(cache.desc), _ptr(q), n_q, operator.index(max_seq_len), _ptr(t_k_inv),
         float(sm_scale), _ptr(out), _ptr(workspace), workspace.numel() * workspace.element_size(),
         _stream_handle(stream))
-    check(st, "wushkv_decode_attention")
+    if st != _lib.OK:
+        _decode_need(cache, n_q, max_seq_len)
+        check(st, "wushkv_decode_attention")
     return out
 
 
@@ -284,16 +307,15 @@ def wushkv_decode_step(cache: WushKVCache, k_new, v_new, n_new, t_k, q, t_k_inv,
         sm_scale = 1.0 / math.sqrt(cache.head_dim)
     if out is None:
         out = torch.empty(cache.batch, n_q, cache.head_dim, dtype=torch.float32, device=q.device)
-    need = wushkv_decode_workspace_bytes(cache, n_q, max_seq_len)
-    if need == 0:
-        raise WushKVError(_lib.EINVAL, "wushkv_decode_workspace_bytes")
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+        workspace = torch.empty(_decode_need(cache, n_q, max_seq_len), dtype=torch.uint8, device=q.device)
     st = _lib.lib().wushkv_decode_step(
         ctypes.byref(cache.desc), _ptr(k_new), _ptr(v_new), _ptr(n_new), _ptr(t_k), _ptr(q), n_q,
-        int(max_seq_len), _ptr(t_k_inv), float(sm_scale), _ptr(out), _ptr(workspace),
+        operator.index(max_seq_len), _ptr(t_k_inv), float(sm_scale), _ptr(out), _ptr(workspace),
         workspace.numel() * workspace.element_size(), _stream_handle(stream))
-    check(st, "wushkv_decode_step")
+    if st != _lib.OK:
+        _decode_need(cache, n_q, max_seq_len)
+        check(st, "wushkv_decode_step")
     return out
 
 
@@ -318,16 +340,16 @@ def wushkv_chunk_attention(cache: WushKVCache, q, t_k_inv, n_tok=None, sm_scale=
     if out is None:
         out = torch.empty(cache.batch, max_tok, n_q, cache.head_dim, dtype=torch.float32,
                           device=q.device)
-    need = wushkv_chunk_workspace_bytes(cache, n_q, max_tok, max_seq_len)
-    if need == 0:
-        raise WushKVError(_lib.EINVAL, "wushkv_chunk_workspace_bytes")
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+        workspace = torch.empty(_chunk_need(cache, n_q, max_tok, max_seq_len), dtype=torch.uint8,
+                                device=q.device)
     st = _lib.lib().wushkv_chunk_attention(
-        ctypes.byref(cache.desc), _ptr(q), _ptr(n_tok), int(max_tok), n_q, int(max_seq_len),
+        ctypes.byref(cache.desc), _ptr(q), _ptr(n_tok), int(max_tok), n_q, operator.index(max_seq_len),
         _ptr(t_k_inv), float(sm_scale), _ptr(out), _ptr(workspace),
         workspace.numel() * workspace.element_size(), _stream_handle(stream))
-    check(st, "wushkv_chunk_attention")
+    if st != _lib.OK:
+        _chunk_need(cache, n_q, max_tok, max_seq_len)
+        check(st, "wushkv_chunk_attention")
     return out
 
 
