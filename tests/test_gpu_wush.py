@@ -115,3 +115,26 @@ def test_wush_transform_drives_the_cache(gpu):
     q = oracle.f32_to_bf16(rng.standard_normal((2, H_ * G, d)).astype(np.float32))
     _, em, er = p.decode_check(q)
     say("  built transform through the cache: rel err %.2e / %.2e" % (em, er))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_outputs_in_the_inputs_place_and_without_the_inverse(gpu, d):
+    """The builder keeps M_d in T^{-1}'s memory while it works and reads a
+    pair's inputs whole before it writes: T is the same bits without an
+    inverse, and written over H or over M; T^{-1} the same over H; and a
+    pair's result does not depend on its neighbours."""
+    M, H, _ = _pairs(3 + d, 3, d)
+    m, h = torch.from_numpy(M).to(gpu), torch.from_numpy(H).to(gpu)
+    say("wush in place d=%d" % d)
+    T, Ti, sw = wk.wushkv_wush_transform(m, h)
+    T2, none, sw2 = wk.wushkv_wush_transform(m, h, want_inverse=False)
+    assert none is None and torch.equal(T, T2) and torch.equal(sw, sw2)
+    for over_m in (False, True):
+        m2, h2 = m.clone(), h.clone()
+        wk.wushkv_wush_transform(m2, h2, t_out=m2 if over_m else h2, want_inverse=False)
+        assert torch.equal(m2 if over_m else h2, T)
+    h2 = h.clone()
+    T3, _, _ = wk.wushkv_wush_transform(m, h2, t_inv_out=h2)
+    assert torch.equal(T3, T) and torch.equal(h2, Ti)
+    T4, Ti4, _ = wk.wushkv_wush_transform(m[1:2].contiguous(), h[1:2].contiguous())
+    assert torch.equal(T4[0], T[1]) and torch.equal(Ti4[0], Ti[1])
