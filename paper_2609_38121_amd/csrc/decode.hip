@@ -710,16 +710,17 @@ __device__ void step_token(const DecodeArgs &a, int b, int h, int32_t slot, uint
 // works this out for itself from the counters (lane l, sequence l: batches of
 // at most 64); the first workgroup notes it for the merge.
 struct PageRun {
-    int32_t b, hi, n_pages;  // the sequence, the end of its quantised positions, its pages
+    int32_t b, s, hi, n_pages;  // the sequence, its length, the end of its quantised positions, its pages
     int32_t first, u;        // the workgroup's first page, pages per wave
     bool idle;
 };
 // One sequence's own workgroups share its pages.
-__device__ __forceinline__ PageRun own_run(const DecodeArgs &a, int b, int split, int32_t hi, int32_t n_pages)
+__device__ __forceinline__ PageRun own_run(const DecodeArgs &a, int b, int split, int32_t S, int32_t hi,
+                                               int32_t n_pages)
 {
     const int32_t P = a.n_page_splits;
     const int32_t u = min(max((n_pages + 4 * P - 1) / (4 * P), 1), 64);
-    return PageRun{b, hi, n_pages, 4 * split * u, u, false};
+    return PageRun{b, S, hi, n_pages, 4 * split * u, u, false};
 }
 struct RunCounters {
     int32_t s, q, nn;  // of sequence `lane` (zeros beyond the batch)
@@ -752,7 +753,8 @@ __device__ __forceinline__ PageRun plan_runs(const DecodeArgs &a, const RunCount
     const bool note = h == 0 && b == 0 && split == 0 && wave == 0;
     if (u >= u_own) {
         if (note && lane == 0) a.runs[0] = 0;
-        return own_run(a, b, split, __builtin_amdgcn_readlane(hi, b), __builtin_amdgcn_readlane(pages, b));
+        return own_run(a, b, split, __builtin_amdgcn_readlane(S, b), __builtin_amdgcn_readlane(hi, b),
+                       __builtin_amdgcn_readlane(pages, b));
     }
     const int32_t end = wave_scan(wgs), start = end - wgs;
     if (note) {
@@ -764,10 +766,10 @@ __device__ __forceinline__ PageRun plan_runs(const DecodeArgs &a, const RunCount
     }
     const int32_t i = b * P + split;
     const uint64_t mine = __ballot(lane < B && start <= i && i < end);
-    if (mine == 0) return PageRun{b, a.s_sink, 0, 0, 1, true};
+    if (mine == 0) return PageRun{b, 0, a.s_sink, 0, 0, 1, true};
     const int l = __builtin_ctzll(mine);
-    return PageRun{l, __builtin_amdgcn_readlane(hi, l), __builtin_amdgcn_readlane(pages, l),
-                   4 * u * (i - __builtin_amdgcn_readlane(start, l)), u, false};
+    return PageRun{l, __builtin_amdgcn_readlane(S, l), __builtin_amdgcn_readlane(hi, l),
+                   __builtin_amdgcn_readlane(pages, l), 4 * u * (i - __builtin_amdgcn_readlane(start, l)), u, false};
 }
 
 // FORM: the workgroup forms q~ and its limbs itself (the grid fits on the
@@ -853,7 +855,7 @@ decode_main_kernel(DecodeArgs a)
         qin.load_q(a, b, tg, h, S, tid);
         if (page_wg && a.even) {
             const PageRun pr = a.runs != nullptr ? plan_runs(a, counters, b, split, h, wave, lane)
-                                                 : own_run(a, b, split, q_hi, n_qpages);
+                                                 : own_run(a, b, split, S, q_hi, n_qpages);
             if (pr.idle) return;
             p_hi = pr.hi;
             w0 = pr.first + wave * pr.u;
@@ -864,7 +866,7 @@ decode_main_kernel(DecodeArgs a)
                 if (a.n_pages > 0 && lane < upw && w0 + lane < a.max_pages)
                     tbl = a.page_table[(int64_t)pr.b * a.max_pages + w0 + lane];
             }
-            if (pr.b != b) qin.load_q(a, pr.b, tg, h, S, tid);
+            if (pr.b != b) qin.load_q(a, pr.b, tg, h, pr.s, tid);
         }
     }
     using Q = QueryLds<D, G>;
@@ -2516,8 +2518,9 @@ static int attend(const wushkv_cache *c, const uint16_t *q, const int32_t *n_tok
     const bool form = !rs.share && p.win_units == 1 &&
                       wgs * 4 <= resident_waves(c->head_dim, storage_bits(c->bits), G, false);
     // such a grid also deals its page runs out by the lengths it finds (one
-    // lane per sequence), noted where the query rows' aux words would be
-    a.even = form && max_tok == 1 && n_tok == nullptr && p.n_page_splits > 0;
+    // lane per sequence), noted where the query rows' aux words would be; a
+    // chunk of one token as a decode, whose bits it keeps
+    a.even = form && max_tok == 1 && p.n_page_splits > 0;
     if (a.even && c->batch > 1 && c->batch <= 64 &&
         p.aux_bytes >= (2 + 2 * (size_t)c->batch) * sizeof(int32_t))
         a.runs = reinterpret_cast<int32_t *>(qaux);

@@ -4,13 +4,16 @@ all, lengths far below max_seq_len, the largest batch that is dealt (64) and
 the first that is not (65), odd and single heads.  The output is the oracle's within the decode
 bar and equals that of a plan that runs in rounds, where nothing is dealt
 out, within the rounding of the partials' fp32 sums (1e-5 of a row's largest
-value, as for any two split plans).  Decode steps over the same batches keep
+value, as for any two split plans), and a chunk of one token has its bits.
+Decode steps over the same batches keep
 the cache bit-exact."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
-from gpu_harness import Pair, rel_err, say
+import paper_2609_38121_amd as wk
+from gpu_harness import Pair, rel_err, say, to_dev_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -46,6 +49,15 @@ def test_ragged_runs(gpu, batch, H, G, d, bits, lengths):
             say("runs batch %d heads %d G %d d %d bits %d max_seq_len %d" % (batch, H, G, d, bits, m))
             out, e, _ = p.decode_check(q, max_seq_len=m)
             assert rel_err(out, ref) <= 1e-5
+        # a chunk of one token is the decode; rows without one are zero
+        nt = (rng.random(batch) < 0.7).astype(np.int32)
+        nt[int(np.argmax(lengths))] = 1
+        live = (nt > 0) & (p.gpu.seq_len.cpu().numpy() > 0)
+        one = wk.wushkv_chunk_attention(p.gpu, to_dev_bf16(q[:, None], p.dev), p.tinv_dev,
+                                        n_tok=torch.from_numpy(nt).to(p.dev), sm_scale=p.sm_scale,
+                                        max_seq_len=top + 8).cpu().numpy()[:, 0]
+        dec = p.decode(q, max_seq_len=top + 8)
+        assert np.array_equal(one[live], dec[live]) and not one[~live].any()
         n = (rng.random(batch) < 0.7).astype(np.int32)
         p.step(_bits(rng, batch, H, d), _bits(rng, batch, H, d), n, q, max_seq_len=top + 8)
         p.check_cache()
