@@ -189,19 +189,24 @@ __device__ __forceinline__ void merge_splits(const MergeRows &r, float *dst, int
 #pragma unroll
         for (int e = 0; e < kPer; ++e) o[e] *= f;
         M = m_new;
-        auto add_rows = [&](const auto &v, int32_t i0) {
+        // kFirst rows from v[at] on, rows i0 .. of the wave, i0 < n: the lanes
+        // i0 .. i0 + kFirst - 1 exist (a lane number is taken modulo 64, and a
+        // pass is a whole number of such batches), with weight 0 from n on
+        static_assert(64 % kFirst == 0 && kMore % kFirst == 0, "no batch of rows crosses the wave's last lane");
+        auto add_rows = [&](const auto &v, int at, int32_t i0) {
 #pragma unroll
-            for (int i = 0; i < (int)(sizeof(v) / sizeof(v[0])); ++i) {
-                // (lane i0 + i holds weight 0 past the end)
+            for (int i = 0; i < kFirst; ++i) {
                 const float wi = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w), i0 + i));
 #pragma unroll
-                for (int e = 0; e < kPer; ++e) o[e] = fmaf(wi, v[i][e], o[e]);
+                for (int e = 0; e < kPer; ++e) o[e] = fmaf(wi, v[at + i][e], o[e]);
             }
         };
-        add_rows(x, 0);
+        add_rows(x, 0, 0);
         for (int32_t i0 = kFirst; i0 < n; i0 += kMore) {
             if (i0 > kFirst) load_rows(y, i0);
-            add_rows(y, i0);
+#pragma unroll
+            for (int at = 0; at < kMore; at += kFirst)
+                if (i0 + at < n) add_rows(y, at, i0 + at);
         }
         k0 += 64;
         fetch(k0);

@@ -286,3 +286,80 @@ class Pair:
             return out_fn(self.ref), 0
         patched, n = tie_patched(self.ref, self.mirror)
         return out_fn(patched), n
+
+
+class HeldCache:
+    """A cache filled with Gaussian tokens, and Eq. (2) in fp64 over it."""
+
+    def __init__(self, gpu, H, G, d, bits, lengths, cap=None):
+        self.gpu, self.H, self.G, self.d = gpu, H, G, d
+        self.batch, self.sm_scale = len(lengths), 1.0 / np.sqrt(d)
+        self.cache = wk.WushKVCache(self.batch, H, d, bits, 4, 32, 8, 0.96, 0.92,
+                                    max_seq_len=cap or max(lengths) + 64, device=gpu)
+        tk, tinv = synth.make_transform(H, d, 1, True)
+        self.tk, self.tinv = to_dev_bf16(tk, gpu), torch.from_numpy(tinv).to(gpu)
+        self.gen = torch.Generator(device=gpu).manual_seed(self.batch + d + bits)
+        self.grow(lengths)
+
+    def randn(self, *shape):
+        return torch.randn(shape, generator=self.gen, device=self.gpu).to(torch.bfloat16)
+
+    def grow(self, lengths):
+        todo = np.asarray(lengths) - self.cache.seq_len.cpu().numpy()
+        for at in range(0, int(todo.max()), 8192):
+            n = np.clip(todo - at, 0, 8192).astype(np.int32)
+            k, v = (self.randn(self.batch, int(n.max()), self.H, self.d) for _ in range(2))
+            wk.wushkv_append(self.cache, k, v, torch.from_numpy(n).to(self.gpu), self.tk)
+
+    def queries(self, *tokens):
+        return self.randn(self.batch, *tokens, self.H * self.G, self.d)
+
+    def splits(self, max_seq_len):
+        """Partials of a row in the decode plan, from its workspace's size."""
+        n_q, up = self.H * self.G, lambda x: -(-x // 256) * 256
+        rows = self.batch * n_q
+        rest = up(rows * self.d * 4) + rows * 768 + up(rows * 16)
+        part = wk.wushkv_decode_workspace_bytes(self.cache, n_q, max_seq_len) - rest
+        assert part % (rows * (self.d + 2) * 4) == 0
+        return part // (rows * (self.d + 2) * 4)
+
+    def decode(self, q, max_seq_len=None):
+        return wk.wushkv_decode_attention(self.cache, q, self.tinv, sm_scale=self.sm_scale, max_seq_len=max_seq_len)
+
+    def attention64(self, b, q, S, end, most=None):
+        """One query token over positions [0, S), those of [sink, end) as
+        their pages hold them (without the pages from number ``most`` on)."""
+        c, sink = self.cache, self.cache.s_sink
+        end = max(end, sink)
+        stored = end - sink if most is None else min(end - sink, 64 * most)
+        k, v = wk.wushkv_dequant(c, b, sink, stored)
+        pos = torch.tensor(list(range(min(S, sink))) + list(range(end, S)), dtype=torch.int64, device=self.gpu)
+        slot = torch.where(pos < sink, pos, sink + (pos - sink) % (c.win_slots - sink))
+        k = torch.cat([k.double(), c.win_k[b][:, slot].double()], 1)
+        v = torch.cat([v.double(), c.win_v[b][:, :, slot].double().transpose(1, 2)], 1)
+        qt = torch.bmm(q.double().view(self.H, self.G, self.d), self.tinv.double())
+        s = torch.bmm(qt, k.transpose(1, 2).contiguous()) * self.sm_scale
+        return torch.bmm(s.softmax(-1), v).view(self.H * self.G, self.d)
+
+    def check(self, out, q, S, end, rows=None, most=None):
+        for b in rows if rows is not None else range(self.batch):
+            e = rel_err(out[b].cpu().numpy(), self.attention64(b, q[b], int(S[b]), int(end[b]), most).cpu().numpy())
+            assert e <= TOL, "sequence %d: rel err %.2e" % (b, e)
+
+    def counters(self):
+        return self.cache.seq_len.cpu().numpy(), self.cache.quant_end.cpu().numpy()
+
+    def check_decode_and_step(self, max_seq_len=None, rows=None):
+        """Decode, a step that appends nothing (the same bits) and one that
+        appends to every sequence (which attends before it flushes)."""
+        q, (S, end) = self.queries(), self.counters()
+        out = self.decode(q, max_seq_len)
+        self.check(out, q, S, end, rows)
+        k, v = self.randn(self.batch, self.H, self.d), self.randn(self.batch, self.H, self.d)
+        for n in (0, 1):
+            got = wk.wushkv_decode_step(self.cache, k, v, torch.full((self.batch,), n, dtype=torch.int32, device=self.gpu),
+                                        self.tk, q, self.tinv, sm_scale=self.sm_scale, max_seq_len=max_seq_len)
+            if n == 0:
+                assert torch.equal(got, out)
+            else:
+                self.check(got, q, S + 1, end, rows)
