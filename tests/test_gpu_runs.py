@@ -13,7 +13,7 @@ import torch
 
 import oracle
 import paper_2609_38121_amd as wk
-from gpu_harness import Pair, rel_err, say, to_dev_bf16
+from gpu_harness import HeldCache, Pair, rel_err, say, to_dev_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -61,3 +61,17 @@ def test_ragged_runs(gpu, batch, H, G, d, bits, lengths):
         n = (rng.random(batch) < 0.7).astype(np.int32)
         p.step(_bits(rng, batch, H, d), _bits(rng, batch, H, d), n, q, max_seq_len=top + 8)
         p.check_cache()
+
+
+@pytest.mark.parametrize("pages,lengths", [(32, [100, 8000, 90, 300, 60, 40, 500, 70]), (16, [100, 60000]), (8, [5000])])
+def test_sequences_longer_than_max_seq_len(gpu, pages, lengths):
+    """max_seq_len is the caller's statement; a replayed graph's sequences may
+    outgrow it.  A sequence's pages past those the grid was sized for are then
+    left out, and every other one is attended to once."""
+    say("runs of %s sized for %d pages" % (lengths, pages))
+    p = HeldCache(gpu, 1, 4, 64, 2, lengths)
+    (S, end), q = p.counters(), p.queries()
+    # (two pages a wave: the grid holds these pages and no more)
+    out = p.decode(q, 4 + 64 * pages)
+    assert p.splits(4 + 64 * pages) == pages // 8 + 1
+    p.check(out, q, S, end, most=pages)
