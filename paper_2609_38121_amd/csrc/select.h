@@ -20,8 +20,6 @@ typedef __attribute__((ext_vector_type(2))) int16_t i16x2;
 // Signed 16-bit order on both halves (magnitudes are below 2^15).
 __device__ __forceinline__ i16x2 sel_max(i16x2 a, i16x2 b) { return __builtin_elementwise_max(a, b); }
 __device__ __forceinline__ i16x2 sel_min(i16x2 a, i16x2 b) { return __builtin_elementwise_min(a, b); }
-__device__ __forceinline__ int32_t sel_max(int32_t a, int32_t b) { return a > b ? a : b; }
-__device__ __forceinline__ int32_t sel_min(int32_t a, int32_t b) { return a < b ? a : b; }
 
 // x[i] the larger, x[j] the smaller.
 template <typename T>
