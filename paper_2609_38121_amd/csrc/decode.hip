@@ -93,7 +93,7 @@ struct DecodeArgs {
     // formed by decode_qt_kernel when the main kernel does not form q~
     // itself (rows (grid row, kv head, query head of the group)):
     float *qt;             // [rows][D], scaled q~
-    uint8_t *qlimb;        // [rows][6][128] fp8 limbs in operand order
+    uint8_t *qlimb;        // [rows][6][128] digit limbs (Limbs) in operand order
     uint32_t *qaux;        // [rows][4]: limb scales (E8M0 bytes, limbs 0-3 then 4-5),
                            // sum(q~) (fp32 bits), unused
     // query rows: G is the number of virtual query heads per kv head, each
@@ -706,9 +706,10 @@ __device__ void step_token(const DecodeArgs &a, int b, int h, int32_t slot, uint
 // fewer pages than its u_own can be had by dealing all the workgroups out in
 // proportion to the pages (sequence l takes ceil(pages_l / (4 u)) consecutive
 // ones, with the least u for which they suffice), they are: eight sequences of
-// 1500 to 12000 tokens, eight heads, 4-bit, take 35.0 us a call instead of 38.2.  Every wave of the launch
-// works this out for itself from the counters (lane l, sequence l: batches of
-// at most 64); the first workgroup notes it for the merge.
+// 1500 to 12000 tokens, eight heads, 4-bit, take 35.0 us a call instead of
+// 38.2.  Every wave of the launch works this out for itself from the counters
+// (lane l, sequence l: batches of at most 64); the first workgroup notes it
+// for the merge.
 struct PageRun {
     int32_t b, s, hi, n_pages;  // the sequence, its length, the end of its quantised positions, its pages
     int32_t first, u;        // the workgroup's first page, pages per wave
@@ -1457,7 +1458,7 @@ decode_main_kernel(DecodeArgs a)
 // eight token groups) takes all 64 query rows of the block -- (chunk token,
 // query head) pairs, eight token groups of G = 8 rows, row r of the block in
 // token group r / 8 -- so that each page leaves HBM once and its codes are
-// unpacked once.  Pages stream through three LDS slots that the four waves
+// unpacked once.  Pages stream through four LDS slots that the four waves
 // share (each wave loads its part of every page).  Per page:
 //   scores  wave w takes rows 16 w .. 16 w + 15: one scaled product per
 //           limb and 16 tokens, whose A rows are the 16 query rows'

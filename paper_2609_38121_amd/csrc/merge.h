@@ -86,11 +86,16 @@ __device__ __forceinline__ float wave_max(float x)
     return fmaxf(q.a, q.b);
 }
 
-// A row is merged by one wave where there are many rows (they fill the device
-// by themselves: 2048 rows of 9 splits take 5.7 us, with four waves a row 7.5),
-// by four otherwise (a row's splits are then a shorter chain: 32 rows of 89
-// splits 4.6 us, 256 rows of 11 splits 4.5 us).  The fused step and the separate calls go by the same rule,
-// so that their outputs are the same bits.
+// A row is merged by one wave where there are many rows, by four otherwise.
+// Many rows fill the device by themselves, so that one wave each is less work:
+// 2048 rows of 4, 10 and 18 splits take 4.1, 4.8 and 5.4 us a launch, with four
+// waves a row 4.4, 5.2 and 5.8; 1024 rows of 34 splits 5.4 and 5.9.  With few
+// rows the launch's own 4 us is nearly all of it, and a row's splits are a
+// shorter chain in four waves, which long contexts feel.  Between 256 and 1536
+// rows of at most 18 splits both take 4.0 us, so the line is drawn where the
+// work begins to show; it costs 1.5 us at 1024 rows of 66 splits (7.5 us, with
+// four waves 6.0; 128 sequences of 262144 tokens).  The fused step and the
+// separate calls go by the same rule, so that their outputs are the same bits.
 constexpr int kMergeWaves = 4;
 __host__ __device__ constexpr bool merge_by_one(int64_t rows) { return rows >= 1024; }
 

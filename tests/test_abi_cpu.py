@@ -237,7 +237,7 @@ def test_workspace_bytes_closed_form():
     d = _desc()
     # partials: one (o[d], m, l) per (sequence, kv head, split, query head
     # of the group); then, for grids formed in rounds, q~: batch * n_q * d * 4
-    # rounded up to 256, six 128-byte fp8 limbs and 16 bytes of scales and
+    # rounded up to 256, six 128-byte limbs and 16 bytes of scales and
     # sum per query head (the latter rounded up to 256).
     # ceil((1000 - 4)/64) = 16 pages per (sequence, head), 2 per wave, 8 per
     # four-wave workgroup -> 2 page splits, plus one workgroup per 64 window

@@ -1,8 +1,9 @@
 """GPU parity of the append's two ways of advancing S and S_quant (Alg. 2
-steps 4 and 7-11): a launch of at most 64 workgroups per sequence counts its
+steps 4 and 7-11): an append of at most 64 workgroups per sequence counts its
 arrivals in the commit array and its last workgroup writes the counters; a
-larger one counts none and a one-workgroup launch after it writes them.
-Appends on both sides of that boundary, one after another on the same cache
+larger one only quantises, counting none, and a second, small launch
+("append_commit") writes the window entries that the first could not and counts
+its own workgroups' arrivals.  Appends on both sides of that boundary, one after another on the same cache
 and with ragged and zero counts, keep the cache bit-exact with the mirror
 and the counters equal to the oracle's, take the path their size calls for,
 and leave the commit array zero."""
@@ -38,7 +39,7 @@ def test_counter_commit_paths(gpu, d, bits, G):
     rng = np.random.default_rng(11 + d + bits)
     B, H = 3, 8
     p = Pair(gpu, B, H, G, d, bits, 4, 128, 8, 0.96, 0.92, cap=2400, seed=3)
-    # (counts, whether the counters take a launch of their own): 8 kv heads
+    # (counts, whether the windows and counters take a launch of their own): 8 kv heads
     # and a grid of 8 tiles make 64 workgroups per sequence, 16 tiles 128
     plan = [([20, 0, 33], False), ([700, 650, 0], True), ([40, 17, 90], False),
             ([0, 900, 310], True), ([25, 25, 25], False)]
