@@ -793,7 +793,7 @@ def bench_prefill(torch, wk, synth, dev, args):
         b_ = byts + (table_bytes if name != "prenormed" else 0)
         ach = b_ / (t_kernel * 1e-3) / 1e9
         log("prefill append (%s): %.1f us/call, %.3g tokens/s, append_kernel %.1f us, %.1f GB/s "
-            "(flush-only launch %.1f us, counter launch %.1f us)"
+            "(flush-only launch %.1f us, window and counter launch %.1f us)"
             % (name, ms * 1e3, tokens / (ms * 1e-3), t_kernel * 1e3, ach, t_flush * 1e3, t_commit * 1e3))
         tkey = {"norm_rope": "traffic_bytes_per_launch", "prenormed": "traffic_bytes_per_launch_prenormed",
                 "quest": "traffic_bytes_per_launch_quest"}[name]
