@@ -715,20 +715,14 @@ struct PageRun {
     int32_t first, u;        // the workgroup's first page, pages per wave
     bool idle;
 };
-// A sequence's quantised pages, of those the grid was sized for: one longer
-// than max_seq_len is cut off there, so that no run, own or dealt out, is
-// longer than units_per_wave pages (at most 64: their table entries sit one to
-// a lane).
-__device__ __forceinline__ int32_t planned_pages(const DecodeArgs &a, int32_t hi)
-{
-    return min((hi - a.s_sink + kPage - 1) / kPage, 4 * a.n_page_splits * a.units_per_wave);
-}
-// One sequence's own workgroups share its pages.
+// One sequence's own workgroups share its pages: of one longer than
+// max_seq_len those the grid was sized for, so that no run is longer than
+// units_per_wave (at most 64 pages: their table entries sit one to a lane).
 __device__ __forceinline__ PageRun own_run(const DecodeArgs &a, int b, int split, int32_t S, int32_t hi,
                                                int32_t n_pages)
 {
     const int32_t P = a.n_page_splits;
-    const int32_t u = max((n_pages + 4 * P - 1) / (4 * P), 1);
+    const int32_t u = min(max((n_pages + 4 * P - 1) / (4 * P), 1), a.units_per_wave);
     return PageRun{b, S, hi, n_pages, 4 * split * u, u, false};
 }
 struct RunCounters {
@@ -749,12 +743,13 @@ __device__ __forceinline__ PageRun plan_runs(const DecodeArgs &a, const RunCount
     const int32_t B = gridDim.z, P = a.n_page_splits;
     const int32_t S = c.s + (c.nn < 0 ? 0 : (c.nn > 1 ? 1 : c.nn));
     const int32_t hi = max(min(c.q, S), a.s_sink);
-    const int32_t pages = planned_pages(a, hi);
-    // (page counts are exact in fp32: at most 2^24 in all)
+    const int32_t pages = (hi - a.s_sink + kPage - 1) / kPage;
+    // (page counts are exact in fp32: at most 2^24 in all, as planned)
     const int32_t most = __builtin_amdgcn_readfirstlane((int32_t)wave_max((float)pages));
     const int32_t all = __builtin_amdgcn_readfirstlane((int32_t)wave_sum((float)pages));
     const int32_t u_own = max((most + 4 * P - 1) / (4 * P), 1);
-    int32_t u = max((all + 4 * P * B - 1) / (4 * P * B), 1), wgs = 0;
+    // (nothing is dealt out where a sequence is longer than max_seq_len)
+    int32_t u = u_own > a.units_per_wave ? u_own : max((all + 4 * P * B - 1) / (4 * P * B), 1), wgs = 0;
     for (; u < u_own; ++u) {
         wgs = (pages + 4 * u - 1) / (4 * u);
         if (__builtin_amdgcn_readfirstlane((int32_t)wave_sum((float)wgs)) <= P * B) break;
@@ -864,13 +859,13 @@ decode_main_kernel(DecodeArgs a)
         qin.load_q(a, b, tg, h, S, tid);
         if (page_wg && a.even) {
             const PageRun pr = a.runs != nullptr ? plan_runs(a, counters, b, split, h, wave, lane)
-                                                 : own_run(a, b, split, S, q_hi, planned_pages(a, q_hi));
+                                                 : own_run(a, b, split, S, q_hi, n_qpages);
             if (pr.idle) return;
             p_hi = pr.hi;
-            const int32_t requested = w0;  // units_per_wave entries from here on: as many as any run's
+            const int32_t requested = w0;
             w0 = pr.first + wave * pr.u;
             w1 = min(w0 + pr.u, pr.n_pages);
-            if (pr.b != b || w0 != requested) {
+            if (pr.b != b || pr.u != upw || w0 != requested) {  // not the run requested above
                 tbl = -1;
                 if (a.n_pages > 0 && lane < pr.u && w0 + lane < a.max_pages)
                     tbl = a.page_table[(int64_t)pr.b * a.max_pages + w0 + lane];
